@@ -56,7 +56,7 @@ KERNEL_NAMES = {
     "force": "k_force (EAM Eq. 1 with the Cr-C forces and the fused kicks; on steps whose "
              "velocities are not observed the full kick without the force store, and the drift)",
     "density": "k_density (rho and F'(rho), with the Cr-C Morse pass in its leading blocks)",
-    "list": "k_list_tiles (Cr-Cr Verlet list build with the Cr-C lists in leading blocks), "
+    "list": "k_list_bricks (Cr-Cr Verlet list build with the Cr-C lists in leading blocks), "
             "launches of steps that rebuilt",
 }
 

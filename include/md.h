@@ -137,7 +137,8 @@ typedef struct md_params {
                            list, read by the passes */
     md_eam_paper_params paper;
     int32_t list_tgt;   /* atoms a work item of the Cr-Cr list build aims at (a launch-shape
-                           choice, 32 .. 256; 0: 224); results do not depend on it */
+                           choice, 32 .. 256; 0: 224): from 224 down, a brick of cells is shared
+                           by 224 / list_tgt blocks; results do not depend on it */
     int32_t pad;
 } md_params;
 

@@ -24,18 +24,12 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Byte offsets of the workspace regions.
 struct Layout {
-  size_t desc, state, tile_rep, row_rep, items, c_rep, misc, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
+  size_t desc, state, tile_rep, c_rep, misc, bk_rep, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
       tf, tfixed, tid, count, start, hcell, hrank, hlist, hsorted, scan_state, hnear, near, fme, p_embed, p_force,
       p_morse, p_kin, dm, dmax_p, tbox_p, total;
 };
 
 constexpr int MISC_INTS = 16;    // rebuild flag, status words
-// The list build takes one block per work item while the item table's capacity is at most
-// this many waves of resident blocks (six per compute unit): measured faster on the
-// 216k-atom film (3 waves: 63 against 76 us per rebuild), slower on the 1M-atom film (15
-// waves: 203 against 196 us, and 6.7 against 4.4 us for a step without a rebuild) and on the
-// 8M-atom film (~110 waves of idle blocks per step), even on the 64-replica ensemble (~32).
-constexpr int LIST_ONE_PER_ITEM_WAVES = 8;
 constexpr int SCAN_CHUNK = 2048; // cells per block of the cell-count scan
 constexpr int64_t DECIDE_IN_BIN_MAX_LOADS = (int64_t)1 << 22;   // part loads over all k_bin blocks
 constexpr int PARTS_REDUCED = 64;   // partial reductions of a large single replica's parts
@@ -48,13 +42,12 @@ struct md_system {
   int nrep;
   std::vector<RepDesc> desc;
   std::vector<int> tile_rep;
-  std::vector<int> row_rep;    // replica of each cell row at capacity
   std::vector<int> c_rep;
   std::vector<int2> chunks;    // energy sums: (first tile, tile count) of each chunk
   int64_t ntot, ctot;
   int ntiles;
-  int nlblk;     // blocks of the list build (most work items)
-  int nrows;     // cell rows at capacity, all replicas
+  int64_t bcap;  // bricks at capacity, all replicas
+  int64_t best;  // bricks expected, all replicas
   int ncell_cr, ncell_all;
   Consts K;
   Layout L;
@@ -70,10 +63,10 @@ struct md_system {
   // (outside md_run always the caller's).  ppt: parts per tile of the last displacement
   // maxima and boxes (1 from the kick-drift pass, T from a force pass with the drift).
   int cur = 0, ppt = 1;
-  // grids of the build kernels that stride over their work (set at bind from the device):
-  // tile kernels (256 threads) and the persistent list build
-  int tile_grid = 2048, list_grid = 2048;
-  int list_tgt = LIST_TGT;   // atoms a list-build work item aims at
+  // grid of the build kernels that stride over their tiles (set at bind from the device)
+  int tile_grid = 2048;
+  int cus = 256;
+  int list_parts = 1;    // blocks per brick in the list build that md_params.list_tgt asks for
   int static_dev = -1;   // device whose static scratch is the workspace (md_workspace_bind_static)
 };
 
@@ -115,8 +108,7 @@ Layout make_layout(const md_system& s) {
   L.desc = take(sizeof(RepDesc) * s.nrep);
   L.state = take(sizeof(RepState) * s.nrep);
   L.tile_rep = take(sizeof(int) * nt);
-  L.row_rep = take(sizeof(int) * (size_t)s.nrows);
-  L.items = take(sizeof(int2) * (size_t)s.nlblk);
+  L.bk_rep = take(s.nrep > 1 ? sizeof(int) * (size_t)s.bcap : 0);
   L.c_rep = take(sizeof(int) * (size_t)s.ctot);
   L.misc = take(sizeof(int) * MISC_INTS);
   L.chunks = take(sizeof(int2) * s.chunks.size());
@@ -145,7 +137,7 @@ Layout make_layout(const md_system& s) {
   L.hlist = take(sizeof(int) * (size_t)s.ctot);
   L.hsorted = take(sizeof(double4) * (size_t)s.ctot);
   L.scan_state = take(sizeof(long long) * (size_t)s.scan_blocks);
-  L.hnear = take(sizeof(int) * (size_t)s.ncell_all);
+  L.hnear = take(sizeof(int) * (size_t)(s.ncell_all - s.ncell_cr));
   L.near = take(sizeof(int) * n);
   L.fme = take(sizeof(double) * 4 * n);
   L.dm = take(sizeof(double) * n);       // M'(P_i) of the paper's form
@@ -205,11 +197,15 @@ int scan_spin_limit() {
   return e ? std::atoi(e) : (1 << 22);
 }
 
-// The list build's work distribution (see build_chain).
-bool list_persistent(const md_system* s) {
-  const char* e = std::getenv("MD_LIST_PERSISTENT");
-  if (e && *e) return std::atoi(e) != 0;
-  return s->nlblk > LIST_ONE_PER_ITEM_WAVES * s->list_grid;
+// Blocks that share a brick in the list build: as list_tgt asks for, or enough that a small
+// system's bricks fill the compute units.
+int list_parts(const md_system* s) {
+  return (int)std::max<int64_t>(s->list_parts, std::min<int64_t>(8, s->cus / std::max<int64_t>(1, s->best)));
+}
+// Blocks of the list build: about as many as there are brick shares (their number is known on
+// the device; the blocks stride over them).
+int list_blocks(const md_system* s) {
+  return (int)std::min<int64_t>(std::min<int64_t>(s->bcap, s->best + s->best / 4 + 8) * list_parts(s), (int64_t)1 << 30);
 }
 
 // Grid of the kernels that walk the near-indenter atoms (one wavefront per atom, grid-stride).
@@ -219,6 +215,8 @@ int near_blocks(const md_system* s) { return std::max(1, std::min(2048, s->ntile
 int morse_fused_blocks(const md_system* s) {
   return (int)std::min<int64_t>(2048, std::max<int64_t>(64, (s->ctot + 11) / 12));
 }
+// The same share in the list build's launch (BRICK_NT threads per block).
+int xlist_blocks(const md_system* s) { return (morse_fused_blocks(s) + 1) / 2; }
 
 }  // namespace
 
@@ -350,7 +348,7 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   if (p->tpa != 1 && p->tpa != 2 && p->tpa != 4 && p->tpa != 8) return MD_ERR_ARG;
   if (p->cap % p->tpa != 0) return MD_ERR_ARG;
   if (p->icap < 0 || p->icap % p->tpa != 0) return MD_ERR_ARG;
-  if (p->list_tgt != 0 && (p->list_tgt < 32 || p->list_tgt > LIST_BLOCK)) return MD_ERR_ARG;
+  if (p->list_tgt != 0 && (p->list_tgt < 32 || p->list_tgt > TILE)) return MD_ERR_ARG;
   if (p->potential != MD_POT_FS && p->potential != MD_POT_PAPER) return MD_ERR_ARG;
   if (p->potential == MD_POT_FS && (!(p->eam.c > 0) || !(p->eam.d > 0) || !(p->eam.d <= p->eam.c)))
     return MD_ERR_ARG;
@@ -368,12 +366,14 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   s->ws = nullptr;
   s->have_embed = s->have_force = false;
   s->list_mix = false;
-  s->list_tgt = p->list_tgt ? p->list_tgt : LIST_TGT;
+  // list_tgt: a brick (about 400 centers) whole at the default 224, shared by more blocks below
+  s->list_parts = p->list_tgt ? std::max(1, (224 + p->list_tgt / 2) / p->list_tgt) : 1;
+  s->bcap = s->best = 0;
   // the list holds pairs within the potential's largest Cr-Cr cutoff + skin
   const double cut = p->potential == MD_POT_PAPER ? std::max(p->paper.rc, p->paper.d * p->paper.re) : p->eam.c;
   const double rlist = cut + p->skin;
   const double rxlist = p->morse.rc + p->skin;
-  int64_t a0 = 0, c0 = 0, nlblk = 0;
+  int64_t a0 = 0, c0 = 0;
   int t0 = 0, g0 = 0;
   std::vector<int> hcells(nrep);
   for (int r = 0; r < nrep; ++r) {
@@ -418,17 +418,16 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
     if (a0 > (int64_t)INT32_MAX / 2 || c0 > (int64_t)INT32_MAX / 2) { delete s; return MD_ERR_ARG; }
     s->desc.push_back(d);
     for (int t = 0; t < ntile; ++t) s->tile_rep.push_back(r);
-    // list build: rows at capacity, each cut into at most nseg runs of cells (twice the
-    // runs of LIST_SEG cells, so that dense rows can be cut finer); one block per run
-    s->desc.back().rb0 = (int)s->row_rep.size();
-    s->desc.back().nseg = 2 * ((d.gcap[0] + LIST_SEG - 1) / LIST_SEG) * ((224 + s->list_tgt - 1) / s->list_tgt);
-    const int64_t nrw = (int64_t)d.gcap[1] * d.gcap[2];
-    nlblk += (int64_t)s->desc.back().nseg * nrw;
-    if ((int64_t)s->row_rep.size() + nrw > (int64_t)INT32_MAX / 2 || nlblk > (int64_t)INT32_MAX / 2) {
-      delete s;
-      return MD_ERR_ARG;
+    {
+      RepDesc& dd = s->desc.back();
+      dd.bcap = (int)std::min<int64_t>(brick_capacity(rd.n, dd.gcap), INT32_MAX / 4);
+      s->bcap += dd.bcap;
+      int gd[3], bn[3];
+      for (int a = 0; a < 3; ++a) gd[a] = cells_along(rd.len[a], rlist);
+      choose_bricks(rd.n, dd.bcap, gd, bn);
+      s->best += std::min<int64_t>(dd.bcap, (int64_t)bn[0] * bn[1] * bn[2]);
+      if (s->bcap > (int64_t)INT32_MAX / 16) { delete s; return MD_ERR_ARG; }
     }
-    s->row_rep.insert(s->row_rep.end(), (size_t)nrw, r);
     s->desc.back().ch0 = (int)s->chunks.size();
     for (int t = 0; t < ntile; t += REDUCE_CHUNK)
       s->chunks.push_back(make_int2(t0 - ntile + t, std::min(REDUCE_CHUNK, ntile - t)));
@@ -453,8 +452,6 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   s->ntot = a0;
   s->ctot = c0;
   s->ntiles = t0;
-  s->nlblk = (int)nlblk;
-  s->nrows = (int)s->row_rep.size();
 
   Consts& K = s->K;
   std::memset(&K, 0, sizeof K);
@@ -551,9 +548,6 @@ int bind_workspace(md_system* s, void* ws, hipStream_t st) {
   if ((e = hip_status(hipMemcpyAsync(at<RepDesc>(s, s->L.desc), s->desc.data(),
                                      sizeof(RepDesc) * s->nrep, hipMemcpyHostToDevice, st))))
     return e;
-  if ((e = hip_status(hipMemcpyAsync(at<int>(s, s->L.row_rep), s->row_rep.data(),
-                                     sizeof(int) * s->nrows, hipMemcpyHostToDevice, st))))
-    return e;
   if ((e = hip_status(hipMemcpyAsync(at<int>(s, s->L.tile_rep), s->tile_rep.data(),
                                      sizeof(int) * s->ntiles, hipMemcpyHostToDevice, st))))
     return e;
@@ -569,11 +563,10 @@ int bind_workspace(md_system* s, void* ws, hipStream_t st) {
   s->ppt = 1;
   // the build kernels that stride over their work fill the chip once: as many blocks as its
   // compute units hold at once
-  int dev = 0, cus = 0, per_cu = 0;
+  int dev = 0, cus = 0;
   if ((e = hip_status(hipGetDevice(&dev)))) return e;
   if ((e = hip_status(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)))) return e;
-  if ((e = hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_list_tiles<MD_LIST_WAVES_RESIDENT>, LIST_BLOCK, 0)))) return e;
-  s->list_grid = std::max(1, cus * std::max(1, per_cu));
+  s->cus = std::max(1, cus);
   s->tile_grid = std::max(1, cus * (2048 / BLOCK));
   return hip_status(hipStreamSynchronize(st));
 }
@@ -632,13 +625,9 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   A.R = at<RepDesc>(s, s->L.desc);
   A.S = at<RepState>(s, s->L.state);
   A.tile_rep = at<int>(s, s->L.tile_rep);
-  A.row_rep = at<int>(s, s->L.row_rep);
-  A.items = at<int2>(s, s->L.items);
-  A.nitems = misc + 2;
-  A.next_item = misc + 4;
-  A.nrows = s->nrows;
-  A.nlblk = s->nlblk;
-  A.list_tgt = s->list_tgt;
+  A.bk_rep = at<int>(s, s->L.bk_rep);
+  A.nbk = misc + 2;
+  A.parts = list_parts(s);
   A.c_rep = at<int>(s, s->L.c_rep);
   A.any = misc + 0;
   A.abort = misc + 3;
@@ -718,18 +707,11 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   int e;
   if (ev0 && (e = hip_status(hipEventRecord(ev0, st)))) return e;
   // the Cr-C lists: leading blocks of the staged Cr-Cr list launch, else a launch of their own
-  A.xblocks = (s->list_mix || s->ctot == 0) ? 0 : morse_fused_blocks(s);
-  // the Cr-Cr list: one block per work item while the item table's capacity is a few waves
-  // of resident blocks (the idle blocks then cost less than taking items from a counter),
-  // else resident blocks that take items from a counter (MD_LIST_PERSISTENT=0/1 in the
-  // environment overrides the choice)
-  A.persistent = list_persistent(s);
+  A.xblocks = (s->list_mix || s->ctot == 0) ? 0 : xlist_blocks(s);
   if (s->list_mix)
     k_list_rows<false><<<s->ntiles, BLOCK, 0, st>>>(s->K, A);
-  else if (A.persistent)
-    k_list_tiles<MD_LIST_WAVES_RESIDENT><<<A.xblocks + std::min(s->nlblk, s->list_grid), LIST_BLOCK, 0, st>>>(s->K, A);
   else
-    k_list_tiles<MD_LIST_WAVES><<<A.xblocks + s->nlblk, LIST_BLOCK, 0, st>>>(s->K, A);
+    k_list_bricks<<<A.xblocks + list_blocks(s), BRICK_NT, 0, st>>>(s->K, A);
   if (ev1 && (e = hip_status(hipEventRecord(ev1, st)))) return e;
   if (s->list_mix && s->ctot > 0) k_xlist<<<A.near_blocks, BLOCK, 0, st>>>(s->K, A);
   return check_launch();

@@ -27,7 +27,7 @@ struct RepDesc {
   int g0, gcap[3];      // Cr-Cr cell grid: first cell (global), allocated dims (the dims in
                         // use along open axes follow the atoms, see RepState)
   int h0, hd[3];        // Cr-C cell grid: first cell (global, after all Cr grids), dims
-  int rb0, nseg;        // list build: first cell row at capacity (global numbering), most runs per row
+  int bcap;             // bricks at capacity
   int ch0, nch;         // energy sums: first chunk of tiles, chunk count
   double ginv[3];       // cells per Angstrom of the Cr grid along periodic axes
   double hinv[3];       // cells per Angstrom of the carbon grid
@@ -53,8 +53,27 @@ struct alignas(64) RepState {
   double gedge[3];        // cell edge of that grid (1 / ginv)
   double qscale;          // fixed-point scale of the shadow positions (a power of two)
   int gd[3];
+  int bn[3];              // bricks along each axis (see BrickGrid)
+  int bk0;                // its first brick in the launch-wide numbering
+  float scr_lo, scr_hi;   // band of the list build's FP32 screen
 };
 
+// The cell grid is cut into bricks (blocks of neighbouring cells, a few hundred atoms): the
+// list build takes one brick per block, and its window -- the brick's cells and one layer
+// around them -- is staged in LDS.
+struct BrickHdr {         // one brick: its cells and its window's rows
+  int nry, nrows;         // window rows along y, in all
+  int x0, x1, y0, z0;     // first cell of the brick, last along x
+  int gx, gy, gz;
+  int xa, xb;             // cells of a row's main piece
+  int g0;                 // the replica's first cell
+  int flags;              // BRICK_WL, BRICK_WR
+};
+constexpr int BRICK_WL = 1, BRICK_WR = 2;   // a cell across the lower / upper x face in each row
+constexpr int BRICK_MAX = 6;       // cells along a brick's edge at most
+constexpr int BRICK_ROWS = 64;     // cell rows of a window at most ((BRICK_MAX + 2)^2)
+constexpr int BRICK_CELLS = BRICK_MAX + 3;   // offsets of cells x0-1 .. x1+2 of a window row
+constexpr int BRICK_ATOMS = 480;   // atoms a brick aims at, at most
 // A Cr-Cr list entry holds the neighbour's slot in its low LIST_IDX_BITS bits and, above
 // them, the neighbour's cell relative to the atom's cell at the build: code = 9 (dz + 1) +
 // 3 (dy + 1) + (dx + 1) with dx, dy, dz in {-1, 0, 1}, counted across periodic faces.
@@ -310,8 +329,9 @@ __device__ __forceinline__ int cell_coord(double x, double lo, double inv, int d
 }
 
 // Block-wide exclusive scan of one int per thread; returns the prefix, *total = block sum.
+template <int NT = BLOCK>
 __device__ __forceinline__ int block_exclusive_scan(int v, int* total) {
-  __shared__ int sh[BLOCK / WAVE];
+  __shared__ int sh[NT / WAVE];
   const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
   int x = v;
 #pragma unroll
@@ -323,7 +343,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* total) {
   __syncthreads();
   int off = 0, tot = 0;
 #pragma unroll
-  for (int i = 0; i < BLOCK / WAVE; ++i) {
+  for (int i = 0; i < NT / WAVE; ++i) {
     if (i < w) off += sh[i];
     tot += sh[i];
   }
@@ -353,14 +373,14 @@ __device__ __forceinline__ void wave_sync() {
 // whole block), and item g belongs to the replica r with pre[r] <= g < pre[r + 1].
 constexpr int FLAT_MAXREP = 2048;
 
-template <class Count>
+template <int NT = BLOCK, class Count>
 __device__ int flat_prefix(int nrep, int* pre, Count count) {
   int carry = 0;
-  for (int r0 = 0; r0 < nrep; r0 += BLOCK) {
+  for (int r0 = 0; r0 < nrep; r0 += NT) {
     const int r = r0 + threadIdx.x;
     const int c = r < nrep ? count(r) : 0;
     int tot;
-    const int ex = block_exclusive_scan(c, &tot);
+    const int ex = block_exclusive_scan<NT>(c, &tot);
     if (r < nrep) pre[r] = carry + ex;
     carry += tot;
   }

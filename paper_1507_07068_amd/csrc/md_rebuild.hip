@@ -11,9 +11,9 @@
 //   k_sort_gather   one lane per slot: rank within its cell by (cell, id), gather the atom
 //                   state into sorted order (so the final order is canonical); atoms in a
 //                   marked carbon cell join the near list
-//   k_list_tiles    one block per run of cells of a cell row: the neighbouring rows are
-//                   staged in LDS, each atom scans its window of them; copies the sorted
-//                   state back.  Its leading blocks build the Cr-C lists (xlist_pass: one
+//   k_list_bricks   one block per brick of cells (md_bricks.hpp): the brick's window is staged
+//                   in LDS, each atom scans its nine cell rows of it; copies the sorted state
+//                   back.  Its leading blocks build the Cr-C lists (xlist_pass: one
 //                   wavefront per near atom).  k_list_rows (one lane per atom from global
 //                   memory, for periodic axes with fewer than 3 cells) is followed by
 //                   k_xlist, the same Cr-C pass as a launch of its own.
@@ -22,6 +22,9 @@
 // a step without a rebuild costs a few empty launches.
 #pragma once
 
+#include <type_traits>
+
+#include "md_bricks.hpp"
 #include "md_device.hpp"
 
 namespace md {
@@ -30,10 +33,8 @@ struct BuildArgs {
   const RepDesc* R;
   RepState* S;
   const int* tile_rep;   // [ntiles]
-  const int* row_rep;    // [nrows] replica of each cell row at capacity
-  int2* items;           // [list-build blocks] work items of k_list_tiles: (row, run | runs << 16)
-  int* nitems;           // work items of this build
-  int* next_item;        // the next work item a k_list_tiles block takes (reset with nitems)
+  int* bk_rep;           // [bricks at capacity] replica of each brick (several replicas only)
+  int* nbk;              // bricks of all replicas
   const int* c_rep;      // [ctot] replica of each carbon
   int* any;              // 1 if some replica rebuilds in this step
   int* abort;            // sticky: a bounded wait of a build gave up; no build runs until
@@ -66,7 +67,7 @@ struct BuildArgs {
                          // zero indenter displacement, the carbon's index (as bits) in .w
   long long* scan_state; // [scan_blocks] published chunk sums of k_scan
   int* scan_ticket;      // chunk ticket of k_scan
-  int* hnear;            // [ncell_all]: carbon cell c has a carbon in its 27-cell stencil
+  int* hnear;            // [carbon cells]: the cell has a carbon in its 27-cell stencil
   int* idx;
   int* cnt;
   int* xidx;
@@ -74,19 +75,16 @@ struct BuildArgs {
   int* near;             // [ntot]: replica r's near atoms at near[a0_r ...]
   double* fme;           // [ntot][4]: last Morse force and energy per atom (0 if none)
   int ncell_all, ncell_cr, ntiles, ctot;
+  int parts;             // blocks that share a brick in the list build
   int nbin;              // tile blocks' worth of work of k_bin, k_scatter, k_sort_gather: the Cr
                          // tiles, then 256-carbon groups (the grids stride over them)
   int near_blocks;       // grid of k_xlist
-  int xblocks;           // leading blocks of k_list_tiles that build the Cr-C lists (0: none)
-  int persistent;        // k_list_tiles: blocks take work items from a counter (else one block
-                         // per item of the table's capacity, the blocks past the items idle)
+  int xblocks;           // leading blocks of k_list_bricks that build the Cr-C lists (0: none)
   int commit_ref;        // k_scan records the indenter position of this build (k_bin decided)
   int copy_f;            // the forces are permuted with the atoms (0 inside md_run: no kick reads
                          // them before the next force pass that stores them)
   int scan_chunk, scan_blocks;
   int spin_limit;        // polls of k_scan's look-back before it gives up (< 0: at once)
-  int nrows, nlblk;      // cell rows at capacity; capacity of the work-item table
-  int list_tgt;          // atoms a work item aims at (<= LIST_BLOCK)
 };
 
 #ifndef MD_LIST_BATCH
@@ -99,33 +97,15 @@ constexpr int MAXC = 512;           // candidates staged per window in k_xlist
 #endif
 constexpr int SG_KEYS = MD_SG_KEYS;   // keys of a cell k_sort_gather loads at a time
 constexpr int WAVES_PER_BLOCK = BLOCK / WAVE;
-constexpr int LIST_SEG = 42;      // most cells of one work item of k_list_tiles
-#ifndef MD_LIST_STAGE
-#define MD_LIST_STAGE 1024
-#endif
-constexpr int LIST_STAGE = MD_LIST_STAGE;   // candidates k_list_tiles stages in LDS at a time
 #ifndef MD_LIST_WAVES
-#define MD_LIST_WAVES 7
+#define MD_LIST_WAVES 6
 #endif
-#ifndef MD_LIST_WAVES_RESIDENT
-#define MD_LIST_WAVES_RESIDENT 6
-#endif
-#ifndef MD_LIST_BLOCK
-#define MD_LIST_BLOCK 256
-#endif
-#ifndef MD_LIST_TGT
-#define MD_LIST_TGT 224
-#endif
-constexpr int LIST_BLOCK = MD_LIST_BLOCK;           // threads of k_list_tiles
-constexpr int LIST_TGT = MD_LIST_TGT;               // atoms per work item aimed at (default)
-constexpr int LIST_PT = LIST_STAGE / LIST_BLOCK;    // candidates each thread stages per piece
-static_assert(LIST_STAGE % LIST_BLOCK == 0, "a piece is a whole number of candidates per thread");
-static_assert(LIST_TGT <= LIST_BLOCK, "a work item's atoms aimed at fit one pass of the threads");
 #ifndef MD_LIST_GROUP
 #define MD_LIST_GROUP 4
 #endif
-constexpr int LIST_GROUP = MD_LIST_GROUP;   // candidates screened together per atom in k_list_tiles
-static_assert(LIST_GROUP >= 1 && LIST_GROUP <= 32, "a group's passing bits fit the 32-bit mask k_list_tiles appends from");
+constexpr int LIST_GROUP = MD_LIST_GROUP;   // candidates screened together per atom in k_list_bricks
+static_assert(LIST_STAGE % LIST_GROUP == 0, "whole groups");
+static_assert(LIST_GROUP >= 1 && LIST_GROUP <= 32, "a group's passing bits fit the 32-bit mask k_list_bricks appends from");
 
 
 __device__ __forceinline__ bool rebuild_off(const BuildArgs& A) { return *A.any == 0; }
@@ -195,9 +175,10 @@ __device__ __forceinline__ BuildGrid decide_grid(const Consts& K, const BuildArg
 }
 
 // Records the outcome in the replica's state (one thread).
-__device__ __forceinline__ void record_grid(RepState& s, const BuildGrid& g) {
+__device__ __forceinline__ void record_grid(const Consts& K, const RepDesc& d, RepState& s, const BuildGrid& g) {
   s.rebuild = g.need;
   if (!g.need) return;
+  choose_bricks(d.n, d.bcap, g.gd, s.bn);
   s.nnear_old = s.nnear;
   s.nnear = 0;
   for (int a = 0; a < 3; ++a) {
@@ -207,6 +188,18 @@ __device__ __forceinline__ void record_grid(RepState& s, const BuildGrid& g) {
     s.gd[a] = g.gd[a];
   }
   s.qscale = g.qscale;
+  // the list build's FP32 screen (see k_list_rows): the staged coordinate includes the image
+  // shift, which the error bound covers (3 E)
+  const double u = 0x1p-24, R = K.rlist + 1.0;
+  double err = 4.0 * u * (K.rlist_sq + R * R);
+  for (int a = 0; a < 3; ++a) {
+    const double E = g.gd[a] / g.ginv[a] + 2.0 * R;
+    const double eta = u * (3.0 * E + (d.per[a] ? 2.0 * d.len[a] : 0.0) + 3.0 * R);
+    err += 2.0 * R * eta + eta * eta;
+  }
+  const double delta = 2.0 * err + 1e-6;
+  s.scr_lo = (float)(K.rlist_sq - delta);
+  s.scr_hi = (float)(K.rlist_sq + delta);
 }
 
 template <class MaxReduce>
@@ -215,7 +208,7 @@ __device__ __forceinline__ bool decide_replica(const Consts& K, BuildArgs& A, in
                                                bool lead, MaxReduce maxr) {
   const BuildGrid g = decide_grid(K, A, r, dmax_tile, tile_box, force, A.R[r].t0 * ppt, A.R[r].nt * ppt, t0,
                                   tstep, maxr);
-  if (lead) record_grid(A.S[r], g);
+  if (lead) record_grid(K, A.R[r], A.S[r], g);
   return g.need;
 }
 
@@ -252,10 +245,17 @@ __global__ __launch_bounds__(DECIDE_THREADS) void k_decide(Consts K, BuildArgs A
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    *A.any = any_sh;
-    *A.nitems = 0;   // k_scatter lists the list-build work items of a rebuild
-    *A.next_item = 0;
+  if (threadIdx.x == 0) *A.any = any_sh;
+  if (any_sh) {   // launch-wide numbering of the bricks
+    int carry = 0;
+    for (int r0 = 0; r0 < K.nrep; r0 += DECIDE_THREADS) {
+      const int r = r0 + threadIdx.x;
+      int tot;
+      const int ex = block_exclusive_scan<DECIDE_THREADS>(r < K.nrep ? brick_count(A.S[r].bn) : 0, &tot);
+      if (r < K.nrep) A.S[r].bk0 = carry + ex;
+      carry += tot;
+    }
+    if (threadIdx.x == 0) *A.nbk = carry;
   }
   for (int r = threadIdx.x; r < K.nrep; r += DECIDE_THREADS) {   // builds are counted here
     RepState& s = A.S[r];
@@ -355,11 +355,13 @@ __global__ __launch_bounds__(BLOCK) void k_bin(Consts K, BuildArgs A, const doub
                      [](double v) { return block_max<BLOCK>(v); });
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       RepState& s0 = A.S[0];
-      record_grid(s0, g1);
-      if (g1.need) s0.nbuilds += 1;
+      record_grid(K, A.R[0], s0, g1);
       *A.any = g1.need;
-      *A.nitems = 0;   // k_scatter lists the list-build work items of a rebuild
-      *A.next_item = 0;
+      if (g1.need) {
+        s0.nbuilds += 1;
+        s0.bk0 = 0;
+        *A.nbk = brick_count(s0.bn);
+      }
     }
     if (!g1.need) return;
   } else if (rebuild_off(A)) {
@@ -511,49 +513,17 @@ __global__ __launch_bounds__(BLOCK) void k_scan(BuildArgs A) {
   for (int u = 0; u < SCAN_PER_THREAD; ++u) {
     if (c0 + u < A.ncell_all) {
       A.start[c0 + u] = run;
-      A.hnear[c0 + u] = 0;
+      if (c0 + u >= A.ncell_cr) A.hnear[c0 + u - A.ncell_cr] = 0;
     }
     run += v[u];
   }
 }
 
-// Work items of k_list_tiles for cell row g (capacity numbering) of a rebuilding replica:
-// the row is cut into as many runs of cells as keep a run's atoms near list_tgt (and no run
-// longer than LIST_SEG cells); empty rows get none.  Returns the number of runs.
-__device__ __forceinline__ int row_runs(const BuildArgs& A, int64_t g) {
-  if (g >= A.nrows) return 0;
-  const int r = A.row_rep[g];
-  const RepState& S = A.S[r];
-  if (!S.rebuild) return 0;
-  const RepDesc& d = A.R[r];
-  const int gx = S.gd[0], gy = S.gd[1], gz = S.gd[2];
-  const int l = (int)(g - d.rb0), cy = l % gy, cz = l / gy;
-  if (cz >= gz) return 0;
-  const int crow = d.g0 + (cz * gy + cy) * gx;
-  const int n = A.start[crow + gx] - A.start[crow];
-  if (n == 0) return 0;
-  return min(min(d.nseg, gx), max((gx + LIST_SEG - 1) / LIST_SEG, (n + A.list_tgt - 1) / A.list_tgt));
-}
-
 __global__ __launch_bounds__(BLOCK) void k_scatter(Consts K, BuildArgs A) {
   if (rebuild_off(A)) return;
-  // list-build work items, one cell row per thread, appended with one atomic per wavefront
-  // (their order is immaterial: each item writes only its own atoms' lists)
-  const int lane = threadIdx.x % WAVE;
-  for (int64_t g0 = (int64_t)blockIdx.x * BLOCK; g0 < A.nrows; g0 += (int64_t)gridDim.x * BLOCK) {
-    const int64_t g = g0 + threadIdx.x;
-    const int nr = row_runs(A, g);
-    int incl = nr;   // inclusive prefix over the wavefront
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-      const int t = __shfl_up(incl, o, WAVE);
-      if (lane >= o) incl += t;
-    }
-    int base = 0;
-    if (lane == WAVE - 1 && incl > 0) base = atomicAdd(A.nitems, incl);
-    base = __shfl(base, WAVE - 1, WAVE);
-    for (int k = 0, at = base + incl - nr; k < nr; ++k, ++at)
-      if (at < A.nlblk) A.items[at] = make_int2((int)g, k | (nr << 16));
+  for (int r = blockIdx.x; K.nrep > 1 && r < K.nrep; r += gridDim.x) {   // the bricks' replicas
+    const int b0 = A.S[r].bk0, nb = brick_count(A.S[r].bn);
+    for (int t = threadIdx.x; t < nb; t += BLOCK) A.bk_rep[b0 + t] = r;
   }
   for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) {   // (b uniform over the block)
   if (b < A.ntiles) {
@@ -592,7 +562,7 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(Consts K, BuildArgs A) {
       // registers first: a store could alias it and would make every read after it wait.
       const int h0 = d.h0, hd0 = d.hd[0], hd1 = d.hd[1], hd2 = d.hd[2];
       const int p0 = d.per[0], p1 = d.per[1], p2 = d.per[2];
-      int* __restrict__ hn = A.hnear + h0;
+      int* __restrict__ hn = A.hnear + (h0 - A.ncell_cr);
       const int lc = hid - h0;
       const int hx = lc % hd0, hy = (lc / hd0) % hd1, hz = lc / (hd0 * hd1);
       const int msx = stencil_n(hd0, p0), msy = stencil_n(hd1, p1), msz = stencil_n(hd2, p2);
@@ -666,7 +636,7 @@ __global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
       if (d.nc > 0) {   // in the stencil of an occupied carbon cell: the atom gets a Cr-C list
         int hx, hy, hz;
         c_cell_coords(d, qe.x, qe.y, qe.z, hx, hy, hz);
-        near = A.hnear[d.h0 + (hz * d.hd[1] + hy) * d.hd[0] + hx] != 0;
+        near = A.hnear[d.h0 - A.ncell_cr + (hz * d.hd[1] + hy) * d.hd[0] + hx] != 0;
       }
     }
     const int lane = threadIdx.x % WAVE;
@@ -871,14 +841,15 @@ __global__ __launch_bounds__(BLOCK) void k_list_rows(Consts K, BuildArgs A) {
 // for the atoms of the near list of each rebuilding replica.  One wavefront per near atom
 // (stride over those of all rebuilding replicas), its lanes sharing the 27 carbon cells
 // around the atom; the passing carbons are compacted in candidate order with a ballot.  Runs
-// in blocks bid of nb blocks of BLOCK threads; cand and pre are the block's LDS scratch
-// (WAVES_PER_BLOCK x MAXC slots, XL_FLAT_MAXREP + 1 prefixes).  Reads the sorted positions
+// in blocks bid of nb blocks of NT threads; cand and pre are the block's LDS scratch
+// (NT / WAVE x MAXC slots, XL_FLAT_MAXREP + 1 prefixes).  Reads the sorted positions
 // (tq) and the near list written by k_sort_gather, so it may run beside the Cr-Cr list build.
 constexpr int XL_FLAT_MAXREP = FLAT_MAXREP - 1;   // replicas of the flattened index space
+template <int NT>
 __device__ __forceinline__ void xlist_pass(const Consts& K, const BuildArgs& A, int (*cand_sh)[MAXC], int* pre,
                                            int bid, int nb) {
   const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
-  const int gw = bid * WAVES_PER_BLOCK + w, nw = nb * WAVES_PER_BLOCK;
+  const int gw = bid * (NT / WAVE) + w, nw = nb * (NT / WAVE);
   auto one = [&](int r, int item) {   // near atom `item` of replica r, on this wavefront
     RepState& S = A.S[r];
     const RepDesc& d = A.R[r];
@@ -941,7 +912,7 @@ __device__ __forceinline__ void xlist_pass(const Consts& K, const BuildArgs& A, 
     }
   };
   if (K.nrep <= XL_FLAT_MAXREP) {   // near atoms of all rebuilding replicas as one index space
-    const int total = flat_prefix(K.nrep, pre, [&](int r) { return A.S[r].rebuild ? A.S[r].nnear : 0; });
+    const int total = flat_prefix<NT>(K.nrep, pre, [&](int r) { return A.S[r].rebuild ? A.S[r].nnear : 0; });
     for (int g = gw; g < total; g += nw) {
       const int r = flat_replica(pre, K.nrep, g);
       one(r, g - pre[r]);
@@ -954,356 +925,276 @@ __device__ __forceinline__ void xlist_pass(const Consts& K, const BuildArgs& A, 
   }
 }
 
-// Cr-Cr lists with LDS-staged candidates (replicas whose periodic axes all have >= 3 list
-// cells).  A work item is a run of cells of one cell row (listed by k_scatter, see
-// row_runs), sized so that one pass of a block's threads covers a run's atoms, one center
-// per thread; a grid that fills the chip once, each block taking items from a counter.  For each of the nine neighbouring cell rows (z-major, then y) the block
-// stages that row's atoms of x-cells x0-1 .. x1+1 -- with the cell seen across a periodic
-// x face placed at the end it is seen from -- into LDS as FP32 coordinates relative to the
-// grid origin plus the row's image shift, with the slot in the fourth word.  The nine
-// staged rows are laid end to end; a center's candidates in one row, x-cells cx-1 .. cx+1,
-// are a contiguous window of it, so the candidate order (rows, along x, by slot) is the
-// same as in k_list_rows and the lists are identical.  All nine rows are staged with one
-// round of loads when they fit LIST_STAGE candidates (else in pieces of that size), so a
-// block waits on few dependent memory round trips.  The FP32 screen and its exact FP64
-// band are those of k_list_rows.
+// Cr-Cr lists over bricks (replicas whose periodic axes all have >= 3 list cells).  A block
+// takes a brick (or one of `parts` shares of its centers), stages the brick's window in LDS as
+// FP32 coordinates relative to the grid origin plus the image shift of the row and of the piece
+// across an x face, with the slot in the fourth word, and gives every center one lane.  A
+// center's candidates in one of its nine neighbouring cell rows (z-major, then y), x-cells
+// cx-1 .. cx+1, are a contiguous range of window positions, so the candidate order (rows, along
+// x, by slot) is the same as in k_list_rows and the lists are identical.  The FP32 screen and its
+// exact FP64 band are those of k_list_rows.
+//
+// A window over LIST_STAGE atoms is staged in pieces of that size.  Where a block's centers leave
+// threads over (large cells, a share of a brick), the lanes of a center take its candidates in
+// runs and place their entries after a prefix over the lanes.
+//
+// Bound by VALU work (about 0.7 of the issue slots; the screen and the append loop), with the
+// partly filled lines of the entry stores behind it.  Against one block per run of cells of a
+// single cell row, which staged nine windows' worth of atoms per center instead of 3.4 and had
+// one lane per center (us per rebuild): 174 against 198 on the 1M-atom film, 50 against 62 on
+// the 216k-atom one, 460 against 620 with the paper's form, 1.4 against 4.9 ms for its outer
+// lists, 65 against 240 on the 10k-atom film, 19 against 38 on a 2k-atom bulk; even on the
+// 8M-atom film (1.30 ms).  Held to 6 wavefronts per SIMD (three blocks per compute unit): at 5
+// two blocks fit and the 8M film takes 1.55 ms, at 7 or 8 the registers spill (1.46).
 
-// Image shift (FP64) of neighbouring row rr (z-major, then y) of the row (cy, cz).
-__device__ __forceinline__ void row_shift(int rr, int cy, int cz, int gy, int gz, int per1, int per2,
-                                          double len1, double len2, double& shy, double& shz) {
-  const int uz = cz + rr / 3 - 1, uy = cy + rr % 3 - 1;
-  shz = per2 ? (uz < 0 ? -len2 : (uz >= gz ? len2 : 0.0)) : 0.0;
-  shy = per1 ? (uy < 0 ? -len1 : (uy >= gy ? len1 : 0.0)) : 0.0;
+// Image shift (FP64) along an axis of an unwrapped cell coordinate u of a grid of g cells.
+__device__ __forceinline__ double cell_shift(int u, int g, int per, double len) {
+  return per ? (u < 0 ? -len : (u >= g ? len : 0.0)) : 0.0;
 }
 
-// Occupancy floor: this kernel hides the latency of its LDS and global reads with waves, so
-// its registers are held to what WAVES wavefronts per SIMD can share: MD_LIST_WAVES with one
-// block per work item, MD_LIST_WAVES_RESIDENT for resident blocks that take items from a
-// counter (measured best on the 8M-atom film: 1.42 against 1.46 ms per rebuild at 7, while
-// the 216k-atom film's one block per item does best at 7, 62 against 69 us at 6).
-template <int WAVES>
-__global__ __launch_bounds__(LIST_BLOCK, WAVES) void k_list_tiles(Consts K, BuildArgs A) {
+__global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts K, BuildArgs A) {
   if (rebuild_off(A)) return;
-  __shared__ float4 sq[LIST_STAGE];        // staged candidates: x, y, z, slot bits
-  __shared__ int toff[9][LIST_SEG + 4];    // per row: row-local staged offset of cells x0-1 .. x1+2
-  __shared__ int rinfo[9][2];   // per row: row-local end of the main piece; staged total
-  __shared__ int4 rslot[9];     // per row: slot of row-local candidate g is g + .x (g < .w),
-                                // g + .y (g < end of the main piece), else g + .z
-  __shared__ float2 rsh[9];     // per row: FP32 image shift along y and z
-  static_assert(LIST_BLOCK == BLOCK && sizeof(sq) >= sizeof(int) * (WAVES_PER_BLOCK * MAXC + XL_FLAT_MAXREP + 1),
-                "the Cr-C list blocks run with BLOCK threads in the staging buffer");
+  // staged candidates: x, y, z, slot bits (a group may read past the last)
+  __shared__ float4 sq[LIST_STAGE + LIST_GROUP];
+  __shared__ BrickTab tab;
+  __shared__ int toff[BRICK_ROWS][BRICK_CELLS];   // per row: window position of cells x0-1 .. x1+2
+  __shared__ float2 rsh[BRICK_ROWS];              // per row: FP32 image shift along y and z
+  __shared__ int csh[BRICK_NT], psh[BRICK_NT];    // the centers' counts and slots
+  static_assert(sizeof(sq) >= sizeof(int) * (BRICK_NT / WAVE * MAXC + XL_FLAT_MAXREP + 1),
+                "the Cr-C list blocks work in the staging buffer");
   if ((int)blockIdx.x < A.xblocks) {   // leading blocks: the Cr-C lists
     int* scratch = reinterpret_cast<int*>(sq);
-    xlist_pass(K, A, reinterpret_cast<int(*)[MAXC]>(scratch), scratch + WAVES_PER_BLOCK * MAXC, blockIdx.x,
-               A.xblocks);
+    xlist_pass<BRICK_NT>(K, A, reinterpret_cast<int(*)[MAXC]>(scratch), scratch + BRICK_NT / WAVE * MAXC, blockIdx.x,
+                         A.xblocks);
     return;
   }
-  // the other blocks either stay resident and take work items one at a time from a counter
-  // until none is left (zero items in a step without a rebuild), or take one item each
-  __shared__ int item_sh;
-  const int nitems = uniform(*A.nitems);
-  for (int pass = 0;; ++pass) {
-  if (!A.persistent && pass > 0) break;
-  if (A.persistent) {
-    __syncthreads();   // the previous item's LDS tables and stage are no longer read
-    if (threadIdx.x == 0) item_sh = atomicAdd(A.next_item, 1);
+  const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+  const int total = uniform(*A.nbk) * A.parts, nb = (int)gridDim.x - A.xblocks;
+  // (bricks in launch order: neighbouring ones on different XCDs, so that a batch's rebuilding
+  // replicas spread over the chip)
+  for (int u = (int)blockIdx.x - A.xblocks; u < total; u += nb) {
+    const int brick = A.parts == 1 ? u : u / A.parts, share = u - brick * A.parts;
+    const int r = K.nrep == 1 ? 0 : uniform(A.bk_rep[brick]);
+    RepState& S = A.S[r];
+    if (!uniform(S.rebuild)) continue;
+    const RepDesc& d = A.R[r];
+    const int per[3] = {uniform(d.per[0]), uniform(d.per[1]), uniform(d.per[2])};
+    const double len0 = uniform(d.len[0]), len1 = uniform(d.len[1]), len2 = uniform(d.len[2]);
+    const int sbase = uniform(d.a0 - A.start[d.g0]);   // sorted slot = sbase + start[cell]
+    __syncthreads();   // the previous brick's tables and stage are no longer read
+    if (wave == 0) brick_tables(brick_geom(S.gd, S.bn, per, d.g0, brick - S.bk0), per, A.start, sbase, tab);
     __syncthreads();
-  }
-  const int b = A.persistent ? uniform(item_sh) : (int)blockIdx.x - A.xblocks;
-  if (b >= nitems) break;
-  const int2 it = A.items[b];
-  const int grow = uniform(it.x), sx = uniform(it.y & 0xFFFF), nseg = uniform(it.y >> 16);
-  const int r = uniform(A.row_rep[grow]);
-  RepState& S = A.S[r];
-  const RepDesc& d = A.R[r];
-  const int gx = uniform(S.gd[0]), gy = uniform(S.gd[1]), gz = uniform(S.gd[2]);
-  // descriptor values used in the loops, held in scalar registers
-  const int per0 = uniform(d.per[0]), per1 = uniform(d.per[1]), per2 = uniform(d.per[2]);
-  const double len0 = uniform(d.len[0]), len1 = uniform(d.len[1]), len2 = uniform(d.len[2]);
-  const int l = grow - uniform(d.rb0);
-  const int cy = l % gy, cz = l / gy;
-  const int g0 = uniform(d.g0);
-  const int crow = g0 + (cz * gy + cy) * gx;
-  const int x0 = sx * gx / nseg, x1 = (sx + 1) * gx / nseg - 1;   // this item's cells
-  const int sbase = uniform(d.a0 - A.start[g0]);   // sorted slot = sbase + start[cell]
-  const int cbeg = sbase + uniform(A.start[crow + x0]);
-  const int m = uniform(A.start[crow + x1 + 1]) - (cbeg - sbase);
-  if (m == 0) continue;
-  const double rl2 = K.rlist_sq;
-  const int cap = K.cap, T = K.lt;
-  const int64_t row = K.ntot * T;   // entry k of atom p at idx[(k / T) * row + p * T + k % T]
-  const double4* __restrict__ tq = A.tq;
-  const float4* __restrict__ tqf = A.tqf;
-  const bool shadow = K.shadow;   // entries carry relative cells only for the FP32 shadow
-  // FP32 screen bounds (see k_list_rows); the staged coordinate already includes the image
-  // shift, which the error bound covers
-  float lo_f, hi_f;
-  {
-    const double u = 0x1p-24, R = K.rlist + 1.0;
-    const int gg[3] = {gx, gy, gz};
-    double err = 4.0 * u * (rl2 + R * R);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double E = gg[a] / S.ginv[a] + 2.0 * R;
-      const double eta = u * (3.0 * E + (d.per[a] ? 2.0 * d.len[a] : 0.0) + 3.0 * R);
-      err += 2.0 * R * eta + eta * eta;
-    }
-    const double delta = 2.0 * err + 1e-6;
-    lo_f = uniform((float)(rl2 - delta));
-    hi_f = uniform((float)(rl2 + delta));
-  }
-  const unsigned band_bits = __float_as_uint(hi_f - lo_f);   // hi - lo, exact
-  const int xa = max(x0 - 1, 0), xb = min(x1 + 1, gx - 1);   // main piece of a staged row
-  const bool wl = per0 && x0 == 0, wr = per0 && x1 == gx - 1;   // wrapped end cells
-  const int nt = x1 - x0 + 4;
-  const bool tiny = gx < 3 || gy < 3 || gz < 3;   // a center may meet its own images
-  const float fxl = (float)(-len0), fxr = (float)len0;
-  // the first pass's centers: their loads go out before the tables' round of loads
-  const int cfirst = min((int)threadIdx.x, m - 1);
-  const float4 pf_first = tqf[cbeg + cfirst];
-  const double px_first = tq[cbeg + cfirst].x;
-  {   // the nine rows' tables: all loads first (one round), then the LDS writes
-    constexpr int NIT = (9 * (LIST_SEG + 4) + LIST_BLOCK - 1) / LIST_BLOCK;
-    int tv[NIT], ts[NIT], tl[NIT], tm[NIT], tr[NIT], tL[NIT], tR[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      // every load is unconditional and inside row rw (a row of this replica whether or not
-      // entry t names one), so that none waits on a branch
-      const int t = threadIdx.x + it * LIST_BLOCK;
-      const int rr = min(t / nt, 8), k = t % nt;
-      const bool in = t < 9 * nt;
-      const int z = stencil_cell(cz, rr / 3, gz, per2), y = stencil_cell(cy, rr % 3, gy, per1);
-      const bool row_ok = in && z >= 0 && y >= 0;
-      const int rw = row_ok ? g0 + (z * gy + y) * gx : g0;
-      const int u = min(max(x0 - 1 + k, xa), xb + 1);   // unwrapped cell, clamped
-      const int s_a = A.start[rw + xa], s_m = A.start[rw + xb + 1], s_u = A.start[rw + u];
-      const int s_0 = A.start[rw], s_1 = A.start[rw + 1];
-      const int s_l = A.start[rw + gx - 1], s_r = A.start[rw + gx];
-      ts[it] = s_a;
-      tl[it] = wl ? s_r - s_l : 0;
-      tm[it] = s_m;
-      tr[it] = wr ? s_1 - s_0 : 0;
-      tv[it] = row_ok ? s_u : (in ? -2 : -1);
-      tL[it] = s_l;
-      tR[it] = s_0;
-    }
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int t = threadIdx.x + it * LIST_BLOCK;
-      if (tv[it] == -1) continue;
-      const int rr = t / nt, k = t % nt;
-      int v = 0;
-      if (tv[it] != -2) {
-        const int sa = ts[it], nl = tl[it], nm = tm[it] - sa, nr = tr[it];
-        const int u = x0 - 1 + k;   // unwrapped cell
-        v = u < xa ? 0 : (u <= xb + 1 ? nl + (tv[it] - sa) : nl + nm + nr);
-        if (k == 0) {
-          rinfo[rr][0] = nl + nm;
-          rinfo[rr][1] = nl + nm + nr;
-          rslot[rr] = make_int4(sbase + tL[it], sbase + sa - nl, sbase + tR[it] - (nl + nm), nl);
-          double shy, shz;
-          row_shift(rr, cy, cz, gy, gz, per1, per2, len1, len2, shy, shz);
-          rsh[rr] = make_float2((float)shy, (float)shz);
-        }
-      } else if (k == 0) {
-        rinfo[rr][1] = 0;
+    BrickHdr b;
+    b.nry = uniform(tab.hdr.nry);
+    b.nrows = uniform(tab.hdr.nrows);
+    b.x0 = uniform(tab.hdr.x0);
+    b.x1 = uniform(tab.hdr.x1);
+    b.y0 = uniform(tab.hdr.y0);
+    b.z0 = uniform(tab.hdr.z0);
+    b.gx = uniform(tab.hdr.gx);
+    b.gy = uniform(tab.hdr.gy);
+    b.gz = uniform(tab.hdr.gz);
+    b.xa = uniform(tab.hdr.xa);
+    b.xb = uniform(tab.hdr.xb);
+    const int W = uniform(tab.roff[BRICK_ROWS]), m = uniform(tab.coff[BRICK_ROWS]);   // window, centers
+    const int c_lo = (int)((long long)m * share / A.parts), c_hi = (int)((long long)m * (share + 1) / A.parts);
+    if (c_lo >= c_hi) continue;   // uniform over the block
+    constexpr int CW = 16;   // threads per row of the offsets (BRICK_CELLS of them work)
+    static_assert(CW >= BRICK_CELLS, "a row's offsets");
+    for (int e = threadIdx.x; e < b.nrows * CW; e += BRICK_NT) {
+      const int row = e / CW, k = e % CW, u = b.x0 - 1 + k;   // unwrapped cell
+      if (u > b.x1 + 2) continue;
+      const int rw = tab.rw[row];
+      int v = tab.roff[row];
+      if (rw >= 0)
+        v = u < b.xa ? v : (u <= b.xb + 1 ? v + tab.rp[row].w + (A.start[rw + u] - A.start[rw + b.xa]) : tab.roff[row + 1]);
+      toff[row][k] = v;
+      if (k == 0) {
+        int uy, uz;
+        brick_row(b, row, uy, uz);
+        rsh[row] = make_float2((float)cell_shift(uy, b.gy, per[1], len1), (float)cell_shift(uz, b.gz, per[2], len2));
       }
-      toff[rr][k] = v;
     }
-  }
-  __syncthreads();
-  // start of each row in the staged sequence (scalar registers)
-  int roff[10];
-  roff[0] = 0;
+    const double rl2 = K.rlist_sq;
+    const int cap = K.cap, T = K.lt;
+    // entry k of atom p at idx[(k / T) * lrow + p * T + k % T] (fewer than 2^31 words)
+    const unsigned lrow = (unsigned)K.ntot * T;
+    const double4* __restrict__ tq = A.tq;
+    const float4* __restrict__ tqf = A.tqf;
+    const bool shadow = K.shadow;   // entries carry relative cells only for the FP32 shadow
+    const float lo_f = uniform(S.scr_lo), hi_f = uniform(S.scr_hi);
+    const unsigned band_bits = __float_as_uint(hi_f - lo_f);   // hi - lo, exact
+    const float fxl = (float)(-len0), fxr = (float)len0;
+    // lanes per center: as many (a power of two, up to 16) as let the threads take every center
+    // of this share at once
+    int gsh = 0;
+    while (gsh < 4 && ((c_hi - c_lo) << (gsh + 1)) <= BRICK_NT) ++gsh;
+    const int G = 1 << gsh, gl = lane & (G - 1), NC = BRICK_NT >> gsh;
+    for (int c0 = c_lo; c0 < c_hi; c0 += NC) {
+      const int c = c0 + (threadIdx.x >> gsh);
+      const bool live = c < c_hi;
+      const int crow = brick_center_row(tab, live ? c : c_lo);
+      const int p = tab.cs[crow] + (live ? c : c_lo);
+      const float4 pf = tqf[p];
+      const int cx = cell_coord(tq[p].x, uniform(S.glo[0]), uniform(S.ginv[0]), b.gx);
+      int count = 0;
+      unsigned off = (unsigned)p * T;   // the next entry's place (one lane per center)
+      for (int G0 = 0; G0 < W; G0 += LIST_STAGE) {   // uniform over the block
+        const int nch = min(LIST_STAGE, W - G0);
+        if (c0 == c_lo || W > LIST_STAGE) {   // (else the one piece is still staged)
+          __syncthreads();   // the previous piece is no longer read
+          for (int row = wave; row < b.nrows; row += BRICK_NT / WAVE) {   // a row per wavefront
+            const int ro = uniform(tab.roff[row]), nlm = uniform(tab.nlm[row]);
+            const int g1 = min(uniform(tab.roff[row + 1]), G0 + nch) - ro;
+            const int4 rp = tab.rp[row];
+            const float2 yz = rsh[row];
+            for (int gi = max(0, G0 - ro) + lane; gi < g1; gi += WAVE) {
+              const int j = gi + (gi < rp.w ? rp.x : (gi < nlm ? rp.y : rp.z));
+              const float4 cf = tqf[j];
+              sq[ro + gi - G0] = make_float4(cf.x + (gi < rp.w ? fxl : (gi < nlm ? 0.0f : fxr)), cf.y + yz.x,
+                                             cf.z + yz.y, __int_as_float(j));
+            }
+          }
+          __syncthreads();
+        }
+        if (live) {
+          const int s_self = brick_self(tab, crow, p) - G0;   // the center's own staged position
+#pragma unroll 1
+          for (int rr = 0; rr < 9; ++rr) {   // this center's range of each row
+            const int row = crow + (rr / 3 - 1) * b.nry + (rr % 3 - 1);
+            const int* to = toff[row] + (cx - b.x0);
+            int e0 = to[0], e1 = to[3], b1 = 0, b2 = 0;
+            if (shadow) {
+              b1 = to[1] - G0;
+              b2 = to[2] - G0;
+            }
+            if (W > LIST_STAGE) {   // the piece's part of the range
+              e0 = max(e0, G0) - G0;
+              e1 = min(e1, G0 + nch) - G0;
+            }
+            const int rcode = rr * 3;
+            // exact FP64 test of staged candidate s (in the band, or NaN in the
+            // single-candidate loop)
+            auto exact = [&](int s) {
+              int uy, uz;
+              brick_row(b, row, uy, uz);
+              const double shy = cell_shift(uy, b.gy, per[1], len1), shz = cell_shift(uz, b.gz, per[2], len2);
+              const int gi = G0 + s - tab.roff[row];
+              const double shx = gi < tab.rp[row].w ? -len0 : (gi < tab.nlm[row] ? 0.0 : len0);
+              const double4 pi = tq[p], pj4 = tq[__float_as_int(sq[s].w)];
+              return dist_sq_exact((pj4.x - pi.x) + shx, (pj4.y - pi.y) + shy, (pj4.z - pi.z) + shz) < rl2;
+            };
+            // The range is taken in runs of up to 32 candidates per lane, the center's lanes one
+            // run after the other.  A lane gathers the passing candidates of its run as bits of
+            // one mask and appends them in order together (the appending loop then runs as
+            // often as the most passing candidates of a lane, not once per group screened),
+            // after those of the center's lanes before it.  The center itself occurs once among
+            // its candidates, in the middle row: its bit is cleared.
+            for (int sb = e0; sb < e1;) {
+              const int run = min(32, (e1 - sb + G - 1) >> gsh);
+              const int s0 = sb + gl * run, s1 = min(s0 + run, e1);
+              sb += run << gsh;
+              // LIST_GROUP candidates at a time: the FP32 screen gives their in bits (the last
+              // group's past the run are dropped), and the rare candidates in the band get the
+              // exact test.  d = |r2| - lo: in when negative (its sign bit, shifted into acc); in
+              // the band when 0 <= d < hi - lo, which compares as unsigned bit patterns (both
+              // differences are exact there, by Sterbenz's lemma, and d >= lo beyond 2 lo).  The
+              // absolute value clears the sign of a NaN, which then falls in neither: out, as
+              // the exact test would decide.
+              unsigned acc = 0;
+              int s = s0;
+              for (; s < s1; s += LIST_GROUP) {
+                unsigned dmin = ~0u;
+                float dd[LIST_GROUP];
 #pragma unroll
-  for (int rr = 0; rr < 9; ++rr) roff[rr + 1] = roff[rr] + uniform(rinfo[rr][1]);
-  const int tot = roff[9];
-  for (int c0 = 0; c0 < m; c0 += LIST_BLOCK) {
-    const int c = c0 + threadIdx.x;
-    const bool live = c < m;
-    const int p = cbeg + (live ? c : 0);
-    const float4 pf = c0 == 0 ? pf_first : tqf[p];
-    const int cx = cell_coord(c0 == 0 ? px_first : tq[p].x, uniform(S.glo[0]), uniform(S.ginv[0]), gx);
-    int count = 0;
-    int* __restrict__ wp = A.idx + (int64_t)p * T;
-    auto append = [&](int j) {
-      if (count < cap) *wp = j;
-      ++count;
-      wp += (count & (T - 1)) ? 1 : row - (T - 1);
-    };
-    for (int G0 = 0; G0 < tot; G0 += LIST_STAGE) {   // uniform over the block
-      const int nch = min(LIST_STAGE, tot - G0);
-      if (c0 > 0 || G0 > 0) __syncthreads();   // the previous piece is no longer read
-      {
-        // slot and image shift of each staged position into LDS at once, the coordinate
-        // loads in flight meanwhile; then the coordinates are added in
-        float3 pc[LIST_PT];
+                for (int u = 0; u < LIST_GROUP; ++u) {
+                  const float4 cf = sq[s + u];
+                  const float ex = cf.x - pf.x, ey = cf.y - pf.y, ez = cf.z - pf.z;
+                  dd[u] = fabsf(ex * ex + ey * ey + ez * ez) - lo_f;
+                  acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(dd[u]), 31);
+                  dmin = min(dmin, __float_as_uint(dd[u]));   // one test for the whole group
+                }
+                if (__builtin_expect(dmin < band_bits, 0)) {
 #pragma unroll
-        for (int u = 0; u < LIST_PT; ++u) {
-          const int s = threadIdx.x + u * LIST_BLOCK;
-          if (s < nch) {
-            const int G = G0 + s;
-            int rr = 0, g = G;   // the row of staged position G and its row-local index
-#pragma unroll
-            for (int k = 1; k < 9; ++k)
-              if (G >= roff[k]) {
-                rr = k;
-                g = G - roff[k];
+                  for (int u = 0; u < LIST_GROUP; ++u)
+                    if (__float_as_uint(dd[u]) < band_bits && s + u < s1 && exact(s + u)) acc |= 1u << (LIST_GROUP - 1 - u);
+                }
               }
-            const int4 rs = rslot[rr];
-            const int nlm = rinfo[rr][0];
-            const int j = g + (g < rs.w ? rs.x : (g < nlm ? rs.y : rs.z));
-            const float4* c4 = tqf + j;
-            pc[u] = make_float3(c4->x, c4->y, c4->z);
-            const float2 yz = rsh[rr];
-            sq[s] = make_float4(g < rs.w ? fxl : (g < nlm ? 0.0f : fxr), yz.x, yz.y, __int_as_float(j));
+              // candidate s0 + c at bit 31 - c
+              acc = s1 > s0 ? (acc >> (s - s1)) << (32 - (s1 - s0)) : 0u;
+              if (rr == 4) {
+                const unsigned self = (unsigned)(s_self - s0);
+                if (self < 32u) acc &= ~(0x80000000u >> self);
+              }
+              int k = count, tot = __builtin_popcount(acc);
+              if (G > 1) {   // entries of the center's lanes before this one
+                int incl = tot;
+                for (int o = 1; o < G; o <<= 1) {
+                  const int up = __shfl(incl, lane - o, WAVE);
+                  if (gl >= o) incl += up;
+                }
+                k += incl - tot;
+                tot = __shfl(incl, lane | (G - 1), WAVE);
+              }
+              count += tot;
+              if (G > 1) off = ((unsigned)k >> K.lt_shift) * lrow + (unsigned)p * T + (k & (T - 1));
+              auto append = [&](auto full_c) {   // (full: some entries of these may not fit the capacity)
+                for (; acc; ++k) {
+                  const int at = __builtin_clz(acc), su = s0 + at;
+                  acc &= ~(0x80000000u >> at);
+                  const int code = shadow ? rcode + (su >= b1) + (su >= b2) : 0;
+                  if (!decltype(full_c)::value || k < cap) A.idx[off] = __float_as_int(sq[su].w) | (code << LIST_IDX_BITS);
+                  off += (k + 1) & (T - 1) ? 1u : lrow - (T - 1);
+                }
+              };
+              if (k + __builtin_popcount(acc) <= cap) append(std::false_type{}); else append(std::true_type{});
+            }
           }
         }
-#pragma unroll
-        for (int u = 0; u < LIST_PT; ++u) {
-          const int s = threadIdx.x + u * LIST_BLOCK;
-          if (s < nch) {
-            float4 e = sq[s];
-            e.x += pc[u].x;
-            e.y += pc[u].y;
-            e.z += pc[u].z;
-            sq[s] = e;
-          }
-        }
+      }
+      if (live && gl == 0) {
+        csh[threadIdx.x >> gsh] = min(count, cap);
+        psh[threadIdx.x >> gsh] = p;
+        if (count > cap) atomicMax(&S.overflow, count);
       }
       __syncthreads();
-      if (live) {
-        // the center's staged position (middle row, main piece), relative to this piece
-        const int s_self = roff[4] + (p - rslot[4].y) - G0;
-#pragma unroll 1
-        for (int rr = 0; rr < 9; ++rr) {   // this center's window in each row
-          const int* to = toff[rr] + (cx - x0);
-          const int w0 = roff[rr] + to[0], w1 = roff[rr] + to[3];
-          const int e0 = max(w0, G0) - G0, e1 = min(w1, G0 + nch) - G0;
-          if (e0 >= e1) continue;
-          const int b1 = roff[rr] + to[1], b2 = roff[rr] + to[2];
-          const int rcode = 9 * (rr / 3) + 3 * (rr % 3);
-          // exact FP64 test of staged candidate s (in the band, or NaN in the single-candidate
-          // loop)
-          auto exact = [&](int s) {
-            double shy, shz;
-            row_shift(rr, cy, cz, gy, gz, per1, per2, len1, len2, shy, shz);
-            const int g = G0 + s - roff[rr];
-            const double shx = g < rslot[rr].w ? -len0 : (g < rinfo[rr][0] ? 0.0 : len0);
-            const double4 pi = tq[p], pj4 = tq[__float_as_int(sq[s].w)];
-            return dist_sq_exact((pj4.x - pi.x) + shx, (pj4.y - pi.y) + shy, (pj4.z - pi.z) + shz) < rl2;
-          };
-          // The passing candidates of up to 32 consecutive staged positions from sb on are
-          // gathered as bits of one mask and appended in order together: the appending
-          // loop then runs as often as the most passing candidates of a lane in those 32,
-          // not once per group for the lane with the most in each group.
-          // With three or more cells along every axis the center occurs once among the
-          // staged positions, in the middle row: its bit is cleared from the mask, and
-          // while all of a mask's entries fit under the capacity they are stored with no
-          // further test.  Smaller grids, and a lane about to overflow, test every entry.
-          auto flush = [&](unsigned acc, int sb) {
-            if (!tiny && rr == 4) {
-              const unsigned d = (unsigned)(s_self - sb);
-              if (d < 32u) acc &= ~(1u << d);
-            }
-            if (!tiny && count + __builtin_popcount(acc) <= cap) {
-              for (; acc; acc &= acc - 1) {
-                const int su = sb + __builtin_ctz(acc);
-                const int j = __float_as_int(sq[su].w);
-                *wp = shadow ? j | ((rcode + (su + G0 >= b1) + (su + G0 >= b2)) << LIST_IDX_BITS) : j;
-                ++count;
-                wp += (count & (T - 1)) ? 1 : row - (T - 1);
-              }
-            } else {
-              for (; acc; acc &= acc - 1) {
-                const int su = sb + __builtin_ctz(acc);
-                const int j = __float_as_int(sq[su].w);
-                if (j != p) append(shadow ? j | ((rcode + (su + G0 >= b1) + (su + G0 >= b2)) << LIST_IDX_BITS) : j);
-              }
-            }
-          };
-          unsigned acc = 0;
-          int sb = e0;
-          // LIST_GROUP candidates at a time: the FP32 screen gives their in bits, and the
-          // rare candidates in the band get the exact test
-          int s = e0;
-          for (; s + LIST_GROUP <= e1; s += LIST_GROUP) {
-            if (s - sb > 32 - LIST_GROUP) {   // the same step for every lane of the loop
-              flush(acc, sb);
-              acc = 0;
-              sb = s;
-            }
-            // d = |r2| - lo: in when negative (its sign bit); in the band when
-            // 0 <= d < hi - lo, which compares as unsigned bit patterns (both differences
-            // are exact there, by Sterbenz's lemma, and d >= lo beyond 2 lo).  The absolute
-            // value clears the sign of a NaN, which then falls in neither: out, as the
-            // exact test would decide.
-            unsigned in = 0, dmin = ~0u;
-            float d[LIST_GROUP];
-#pragma unroll
-            for (int u = 0; u < LIST_GROUP; ++u) {
-              const float4 cf = sq[s + u];
-              const float ex = cf.x - pf.x, ey = cf.y - pf.y, ez = cf.z - pf.z;
-              d[u] = fabsf(ex * ex + ey * ey + ez * ez) - lo_f;
-              in |= (__float_as_uint(d[u]) >> 31) << u;
-              dmin = min(dmin, __float_as_uint(d[u]));   // one test for the whole group
-            }
-            if (__builtin_expect(dmin < band_bits, 0)) {
-#pragma unroll
-              for (int u = 0; u < LIST_GROUP; ++u)
-                if (__float_as_uint(d[u]) < band_bits && exact(s + u)) in |= 1u << u;
-            }
-            acc |= in << (s - sb);
-          }
-          for (; s < e1; ++s) {
-            if (s - sb > 31) {
-              flush(acc, sb);
-              acc = 0;
-              sb = s;
-            }
-            const float4 cf = sq[s];
-            const float ex = cf.x - pf.x, ey = cf.y - pf.y, ez = cf.z - pf.z;
-            const float r2f = ex * ex + ey * ey + ez * ez;
-            bool ok = r2f < lo_f;
-            if (__builtin_expect(!ok && !(r2f >= hi_f), 0)) ok = exact(s);
-            acc |= (ok ? 1u : 0u) << (s - sb);
-          }
-          flush(acc, sb);
+      const int nc = min(NC, c_hi - c0);
+      if ((int)threadIdx.x < nc) {   // copy-back of the sorted state, one center per thread
+        const int p = psh[threadIdx.x], kept = csh[threadIdx.x];
+        // all loads before the first store (a store could alias a later load, which would
+        // then wait for it)
+        const double4 pi = tq[p];
+        const double v0 = A.tv[3 * p + 0], v1 = A.tv[3 * p + 1], v2 = A.tv[3 * p + 2];
+        const bool cf = A.copy_f;
+        const double f0 = cf ? A.tf[3 * p + 0] : 0.0, f1 = cf ? A.tf[3 * p + 1] : 0.0, f2 = cf ? A.tf[3 * p + 2] : 0.0;
+        const uint8_t fx = A.tfixed[p];
+        const int ide = A.tid[p];
+        A.cnt[p] = kept;
+        A.q[p] = pi;
+        if (K.shadow) {
+          const int row = brick_center_row(tab, c0 + threadIdx.x);
+          int uy, uz;
+          brick_row(b, row, uy, uz);
+          const long long bc = pack_cell(cell_coord(pi.x, uniform(S.glo[0]), uniform(S.ginv[0]), b.gx), uy, uz);
+          A.bcell[p] = bc;
+          A.qs[p] = cell_local(S, bc, pi.x, pi.y, pi.z, (float)pi.w);
         }
+        A.xref[3 * p + 0] = pi.x;
+        A.xref[3 * p + 1] = pi.y;
+        A.xref[3 * p + 2] = pi.z;
+        A.v[3 * p + 0] = v0;
+        A.v[3 * p + 1] = v1;
+        A.v[3 * p + 2] = v2;
+        if (cf) {
+          A.f[3 * p + 0] = f0;
+          A.f[3 * p + 1] = f1;
+          A.f[3 * p + 2] = f2;
+        }
+        A.fixed[p] = fx;
+        A.id[p] = ide;
       }
+      if (c0 + NC < c_hi) __syncthreads();   // the counts are no longer read
     }
-    if (live) {
-      // all loads before the first store (a store could alias a later load, which would
-      // then wait for it)
-      const double4 pi = tq[p];
-      const double v0 = A.tv[3 * p + 0], v1 = A.tv[3 * p + 1], v2 = A.tv[3 * p + 2];
-      const bool cf = A.copy_f;
-      const double f0 = cf ? A.tf[3 * p + 0] : 0.0, f1 = cf ? A.tf[3 * p + 1] : 0.0, f2 = cf ? A.tf[3 * p + 2] : 0.0;
-      const uint8_t fx = A.tfixed[p];
-      const int ide = A.tid[p];
-      A.cnt[p] = min(count, cap);
-      if (count > cap) atomicMax(&S.overflow, count);
-      A.q[p] = pi;
-      if (K.shadow) {
-        const long long bc = pack_cell(cx, cy, cz);
-        A.bcell[p] = bc;
-        A.qs[p] = cell_local(S, bc, pi.x, pi.y, pi.z, (float)pi.w);
-      }
-      A.xref[3 * p + 0] = pi.x;
-      A.xref[3 * p + 1] = pi.y;
-      A.xref[3 * p + 2] = pi.z;
-      A.v[3 * p + 0] = v0;
-      A.v[3 * p + 1] = v1;
-      A.v[3 * p + 2] = v2;
-      if (cf) {
-        A.f[3 * p + 0] = f0;
-        A.f[3 * p + 1] = f1;
-        A.f[3 * p + 2] = f2;
-      }
-      A.fixed[p] = fx;
-      A.id[p] = ide;
-    }
-  }
   }
 }
 
@@ -1311,7 +1202,7 @@ __global__ __launch_bounds__(BLOCK) void k_xlist(Consts K, BuildArgs A) {
   if (rebuild_off(A)) return;
   __shared__ int cand_sh[WAVES_PER_BLOCK][MAXC];
   __shared__ int pre[XL_FLAT_MAXREP + 1];
-  xlist_pass(K, A, cand_sh, pre, blockIdx.x, gridDim.x);
+  xlist_pass<BLOCK>(K, A, cand_sh, pre, blockIdx.x, gridDim.x);
 }
 
 // Section 2.6's inner list, refilled every step from the outer (Verlet) list: atom i's outer
