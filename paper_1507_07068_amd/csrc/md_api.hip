@@ -30,6 +30,11 @@ struct Layout {
 };
 
 constexpr int MISC_INTS = 16;    // rebuild flag, status words
+// The paper form's passes go over about 200 entries an atom, where 1 or 2 lanes leave few
+// wavefronts in flight and long chains in each: they take 4 lanes per atom, and 8 up to this many
+// atoms.  60 steps of a film, 8 against 4 lanes: 12,800 atoms 0.84 of the time, 41,000 0.97,
+// 52,000 the same, 80,000 1.05, 175,000 1.10.
+constexpr int64_t LANES8_ATOMS = 49152;
 constexpr int SCAN_CHUNK = 2048; // cells per block of the cell-count scan
 constexpr int64_t DECIDE_IN_BIN_MAX_LOADS = (int64_t)1 << 22;   // part loads over all k_bin blocks
 constexpr int PARTS_REDUCED = 64;   // partial reductions of a large single replica's parts
@@ -129,7 +134,7 @@ Layout make_layout(const md_system& s) {
   L.tv = take(sizeof(double) * 3 * n);
   L.tf = take(sizeof(double) * 3 * n);
   L.tfixed = take(n);
-  L.tid = take(sizeof(int) * n);
+  L.tid = L.crank;   // (k_scatter is done with the ranks when k_sort_gather writes the ids)
   L.count = take(sizeof(int) * (size_t)s.ncell_all);
   L.start = take(sizeof(int) * ((size_t)s.ncell_all + 1));
   L.hcell = take(sizeof(int) * (size_t)s.ctot);
@@ -143,11 +148,11 @@ Layout make_layout(const md_system& s) {
   L.dm = take(sizeof(double) * n);       // M'(P_i) of the paper's form
   L.dmax_p = take(sizeof(double) * PARTS_REDUCED);   // k_parts_reduce's partial maxima and boxes
   L.tbox_p = take(sizeof(double) * 6 * PARTS_REDUCED);
-  L.p_embed = take(sizeof(double) * nt * s.K.lt);
-  L.p_force = take(sizeof(double) * nt * s.K.lt * NP_FORCE);
+  L.p_embed = take(sizeof(double) * nt * s.K.ln);
+  L.p_force = take(sizeof(double) * nt * s.K.ln * NP_FORCE);
   // k_kinetic's partials per tile, or those of a force pass that takes them (per block)
-  L.p_morse = take(sizeof(double) * nt * s.K.lt * 4);
-  L.p_kin = take(sizeof(double) * nt * s.K.lt);
+  L.p_morse = take(sizeof(double) * nt * s.K.ln * 4);
+  L.p_kin = take(sizeof(double) * nt * s.K.ln);
   L.total = o;
   return L;
 }
@@ -241,7 +246,8 @@ void launch_density(md_system* s, const md_atoms* a, const md_lists* l, bool mix
 #define DENS(M_, SH, E, PA) \
   k_density<T, M_, SH, E, PA><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, li, lc, rho_out, pe, M, dm)
 #define DENS_P(M_, SH, E) \
-  if (s->K.pot == MD_POT_PAPER) DENS(M_, SH, E, true); else DENS(M_, SH, E, false)
+  if (s->K.pot != MD_POT_PAPER) DENS(M_, SH, E, POT_FS);                     \
+  else if (s->K.P.bh > 0) DENS(M_, SH, E, POT_PAPER); else DENS(M_, SH, E, POT_PAPER_POW)
   if (mixed && s->K.shadow && !s->list_mix) { if (energy) { DENS_P(true, true, true); } else { DENS_P(true, true, false); } }
   else if (mixed) { if (energy) { DENS_P(true, false, true); } else { DENS_P(true, false, false); } }
   else { if (energy) { DENS_P(false, false, true); } else { DENS_P(false, false, false); } }
@@ -272,20 +278,22 @@ void launch_force(md_system* s, const md_atoms* a, const md_lists* l, bool mixed
   const int nb = s->ntiles * T;
   const int4* qs = qscur(s);
   const double* dm = at<double>(s, s->L.dm);
-  const bool paper = s->K.pot == MD_POT_PAPER;
+  const int pot = s->K.pot != MD_POT_PAPER ? POT_FS : s->K.P.bh > 0 ? POT_PAPER : POT_PAPER_POW;
   const int *li = pass_idx(s, l), *lc = pass_cnt(s, l);
 #define FORCE1(M, SH, KI, E, PA)                                                                                \
   k_force<T, M, SH, KI, E, false, PA><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li,     \
                                                              lc, pf, l->xcnt,                                    \
                                                              add_fme ? at<double>(s, s->L.fme) : nullptr, kick_h, D, dm, store_f, KO)
 #define FORCE(M, SH, KI, E) \
-  if (paper) FORCE1(M, SH, KI, E, true); else FORCE1(M, SH, KI, E, false)
+  if (pot == POT_FS) FORCE1(M, SH, KI, E, POT_FS);                                                              \
+  else if (pot == POT_PAPER) FORCE1(M, SH, KI, E, POT_PAPER); else FORCE1(M, SH, KI, E, POT_PAPER_POW)
 #define FORCE_DRIFT1(M, SH, E, PA)                                                                               \
   k_force<T, M, SH, true, E, true, PA><<<nb, BLOCK, 0, st>>>(                                                    \
       s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li, lc, pf, l->xcnt,                                          \
       add_fme ? at<double>(s, s->L.fme) : nullptr, kick_h, D, dm, store_f, KO)
 #define FORCE_DRIFT2(M, SH, E) \
-  if (paper) FORCE_DRIFT1(M, SH, E, true); else FORCE_DRIFT1(M, SH, E, false)
+  if (pot == POT_FS) FORCE_DRIFT1(M, SH, E, POT_FS);                                                            \
+  else if (pot == POT_PAPER) FORCE_DRIFT1(M, SH, E, POT_PAPER); else FORCE_DRIFT1(M, SH, E, POT_PAPER_POW)
 #define FORCE_DRIFT(M, SH) \
   if (energy) { FORCE_DRIFT2(M, SH, true); } else { FORCE_DRIFT2(M, SH, false); }
 #define FORCE_E(M, SH, KI) \
@@ -492,6 +500,8 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   K.nrep = nrep;
   K.lt = p->tpa;
   K.lt_shift = p->tpa == 1 ? 0 : (p->tpa == 2 ? 1 : (p->tpa == 4 ? 2 : 3));
+  K.ln = p->tpa;   // (4 and 8 lanes give the same forces bit for bit: split_sums)
+  if (p->potential == MD_POT_PAPER) K.ln = std::max(p->tpa, s->ntot <= LANES8_ATOMS ? 8 : 4);
   K.shadow = p->shadow ? 1 : 0;
   K.ntot = s->ntot;
   K.pot = p->potential;
@@ -748,7 +758,7 @@ int eam_density(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
     const int e = inner_list(s, a, l, st);
     if (e) return e;
   }
-  switch (s->K.lt) {
+  switch (s->K.ln) {
     case 1: launch_density<1>(s, a, l, mixed, energy, rho_out, morse, st); break;
     case 2: launch_density<2>(s, a, l, mixed, energy, rho_out, morse, st); break;
     case 4: launch_density<4>(s, a, l, mixed, energy, rho_out, morse, st); break;
@@ -763,7 +773,7 @@ int eam_density(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
 int eam_force(md_system* s, const md_atoms* a, const md_lists* l, uint32_t flags, bool add_fme, hipStream_t st,
               bool full_kick = false, bool drift = false, bool fuse_ke = false) {
   const bool mixed = flags & MD_F_MIXED, energy = flags & MD_F_ENERGY, kick = flags & MD_F_KICK;
-  switch (s->K.lt) {
+  switch (s->K.ln) {
     case 1: launch_force<1>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke); break;
     case 2: launch_force<2>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke); break;
     case 4: launch_force<4>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke); break;
@@ -842,8 +852,8 @@ namespace {
 // (KinOut) with the drift, has moved the indenter on and kept the observed step's position).
 int energy_sums(md_system* s, double* out, int tpk, bool ind_obs, hipStream_t st) {
   k_reduce_chunks<<<(int)s->chunks.size(), BLOCK, 0, st>>>(
-      at<int2>(s, s->L.chunks), s->have_embed ? at<double>(s, s->L.p_embed) : nullptr, s->K.lt,
-      s->have_force ? at<double>(s, s->L.p_force) : nullptr, s->K.lt, at<double>(s, s->L.p_morse),
+      at<int2>(s, s->L.chunks), s->have_embed ? at<double>(s, s->L.p_embed) : nullptr, s->K.ln,
+      s->have_force ? at<double>(s, s->L.p_force) : nullptr, s->K.ln, at<double>(s, s->L.p_morse),
       at<double>(s, s->L.p_kin), tpk, at<double>(s, s->L.chunk_out));
   k_reduce<<<s->nrep, BLOCK, 0, st>>>(at<RepDesc>(s, s->L.desc), at<RepState>(s, s->L.state),
                                       at<double>(s, s->L.chunk_out), out, ind_obs ? 1 : 0);
@@ -911,13 +921,13 @@ MD_API int md_run(md_system* s, const md_atoms* a, const md_lists* l, int32_t ns
     }
     if (drift) {
       s->cur ^= 1;
-      s->ppt = s->K.lt;
+      s->ppt = s->K.ln;
     }
     drifted = drift;
     whole = !(full || fuse);
     if (en) {
       double* out = obs + (int64_t)(k / energy_every - 1) * s->nrep * MD_NOBS;
-      if ((e = fuse ? energy_sums(s, out, s->K.lt, drift, st) : md_energy(s, a, out, stream))) return e;
+      if ((e = fuse ? energy_sums(s, out, s->K.ln, drift, st) : md_energy(s, a, out, stream))) return e;
     }
   }
   if (s->cur) {   // the positions back into the caller's q

@@ -111,31 +111,38 @@ struct PaperConsts {
   int bh;             // beta / 2 when it is a whole number 1..8 (then f needs r^2 only), else 0
 };
 
-// f(r) = fe (re / r)^beta from r^2 and 1/r: (re^2 / r^2)^(beta/2) by repeated squaring when
-// beta / 2 is a whole number, else through pow.
-__device__ __forceinline__ double paper_f(const PaperConsts& P, double rinv) {
-  if (P.bh > 0) {
-    const double t = P.re2 * (rinv * rinv);
-    double f = 1.0, b = t;
-    for (int e = P.bh; e; e >>= 1) {   // uniform over the wavefront
-      if (e & 1) f *= b;
-      b *= b;
-    }
-    return P.fe * f;
+// The kernels' potential: the synthetic form, or the paper's with beta / 2 a whole number 1..8
+// (bh > 0) or not.  (The two paper forms are two instances, because pow and its registers would
+// otherwise lie in every pair loop.)
+enum Pot { POT_FS = 0, POT_PAPER = 1, POT_PAPER_POW = 2 };
+
+// t^e for a whole e >= 1, the same in every lane: repeated squaring, with e = 2, 3 and 4 (beta
+// of 4, 6 and 8) straight, as a loop there would cost more than the products.
+template <class V>
+__device__ __forceinline__ V whole_pow(V t, int e) {
+  const V t2 = t * t;
+  if (e == 3) return t * t2;
+  if (e == 2) return t2;
+  if (e == 4) return t2 * t2;
+  V f = (e & 1) ? t : (V)1, b = t2;
+  for (e >>= 1; e; e >>= 1) {
+    if (e & 1) f *= b;
+    b *= b;
   }
-  return P.fe * pow(P.re * rinv, P.beta);
+  return f;
 }
+
+// f(r) = fe (re / r)^beta from 1/r: (re^2 / r^2)^(beta/2) when beta / 2 is a whole number, else
+// through pow.
+template <int POT>
+__device__ __forceinline__ double paper_f(const PaperConsts& P, double rinv) {
+  if constexpr (POT == POT_PAPER_POW) return P.fe * pow(P.re * rinv, P.beta);
+  else return P.fe * whole_pow(P.re2 * (rinv * rinv), P.bh);
+}
+template <int POT>
 __device__ __forceinline__ float paper_f32(const PaperConsts& P, float rinv) {
-  if (P.bh > 0) {
-    const float t = (float)P.re2 * (rinv * rinv);
-    float f = 1.0f, b = t;
-    for (int e = P.bh; e; e >>= 1) {
-      if (e & 1) f *= b;
-      b *= b;
-    }
-    return (float)P.fe * f;
-  }
-  return (float)P.fe * __powf((float)P.re * rinv, (float)P.beta);
+  if constexpr (POT == POT_PAPER_POW) return (float)P.fe * __powf((float)P.re * rinv, (float)P.beta);
+  else return (float)P.fe * whole_pow((float)P.re2 * (rinv * rinv), P.bh);
 }
 
 // Per atom: F(rho), F'(rho) (0 without neighbours), M(P), M'(P) of Eq. A3, in FP64.
@@ -181,6 +188,7 @@ struct Consts {
   int nrep;
   int lt;                 // list interleave: entries k..k+lt-1 of an atom are adjacent
   int lt_shift;           // log2(lt)
+  int ln;                 // lanes per atom of the density and force passes (lt, or more for long lists)
   int shadow;             // 1: keep the FP32 cell-local shadow of the positions
   int pot;                // MD_POT_FS or MD_POT_PAPER
   int64_t ntot;           // atom slots (all replicas)

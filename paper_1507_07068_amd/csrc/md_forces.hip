@@ -7,7 +7,7 @@
 //   k_kick         Task 5 on its own
 //
 // T lanes cooperate on one atom (entries k = sub, sub + T, ... of its list; the list is
-// interleaved by T so those lanes read adjacent words) and combine their partial sums with
+// interleaved by md_params.tpa, and T is that or more: see Consts::ln) and combine their partial sums with
 // a fixed butterfly, so results do not depend on scheduling.  Each atom's sums are written
 // by one lane only: no atomics.
 #pragma once
@@ -28,24 +28,51 @@ __device__ __forceinline__ V group_sum(V v) {
 
 // Visit the entries k = sub, sub + T, ... (< n) of atom i's list in order, calling
 // body(fetch(e), e) for each entry e (the neighbour's slot and relative cell, see
-// list_slot / list_code).  Entries go U at a time: the U gathers of one group are in
+// list_slot / list_code), or body(fetch(e), e, m) with m of the right parity for the lane's
+// m-th entry.  Entries go U at a time: the U gathers of one group are in
 // flight together with the U index loads of the next.
+// The paper's form with 4 lanes per atom keeps a lane's even and odd entries apart (1: two sums,
+// picked by the entry's parity), so that its sums are, bit for bit, those of 8 lanes: the launch
+// may then pick 4 or 8 by the size of the whole batch, and a replica's forces still do not
+// depend on what it is batched with.
+__host__ __device__ constexpr int split_sums(int t, int pot) { return t == 4 && pot != POT_FS; }
+
+// Left to itself the compiler fuses products and sums one way for the entries of a group and
+// another for those left over.  The paper form's pair terms say where they fuse, so that a pair
+// rounds the same wherever it comes in a lane's entries (the agreement of 4 and 8 lanes needs it).
+template <class V>
+__device__ __forceinline__ V sum_sq(V x, V y, V z) {
+  return __builtin_elementwise_fma(z, z, __builtin_elementwise_fma(y, y, x * x));
+}
+template <class V>
+__device__ __forceinline__ V sq_exact(V f) {
+#pragma clang fp contract(off)
+  return f * f;
+}
+
 #ifndef MD_UNROLL
 #define MD_UNROLL 2
 #endif
 constexpr int UNROLL = MD_UNROLL;
+static_assert(UNROLL % 2 == 0, "the parity of an entry is that of its place in the group");
+
+template <class Body, class V>
+__device__ __forceinline__ void visit(Body& body, const V& p, int e, int u) {
+  if constexpr (std::is_invocable_v<Body&, const V&, int, int>) body(p, e, u);
+  else body(p, e);
+}
 
 template <int T, int U, class Fetch, class Body>
 __device__ __forceinline__ void for_entries(const int* __restrict__ idx, int i, int n, int sub, int ntot,
-                                            int shift, Fetch fetch, Body body) {
-  // this lane's entries k = sub + m T (m = 0 .. nl - 1) sit one stride apart, at
-  // idx[(m ntot + i) T + sub]; 32-bit word offsets (the list holds fewer than 2^31 words),
-  // running by the stride, and the index loads ahead clamped to the last entry so that they
-  // need no branch
-  const int nl = n > sub ? ((n - 1 - sub) >> shift) + 1 : 0;
+                                            int lshift, Fetch fetch, Body body) {
+  // with the list interleaved by t = 1 << lshift (t <= T), this lane's entries k = sub + m T
+  // (m = 0 .. nl - 1) sit one stride apart, the first at idx[((sub / t) ntot + i) t + sub % t];
+  // 32-bit word offsets (the list holds fewer than 2^31 words), running by the stride, and the
+  // index loads ahead clamped to the last entry so that they need no branch
+  const int nl = n > sub ? (n - 1 - sub) / T + 1 : 0;
   if (nl == 0) return;
   const unsigned stride = (unsigned)ntot * T;
-  const unsigned first = (unsigned)i * T + sub;
+  const unsigned first = ((((unsigned)sub >> lshift) * (unsigned)ntot + (unsigned)i) << lshift) + ((unsigned)sub & ((1u << lshift) - 1u));
   const unsigned last = first + (unsigned)(nl - 1) * stride;
   unsigned base = first;   // offset of entry m
   int e[U];
@@ -61,14 +88,14 @@ __device__ __forceinline__ void for_entries(const int* __restrict__ idx, int i, 
 #pragma unroll
     for (int u = 0; u < U; ++u) en[u] = idx[min(base + u * stride, last)];
 #pragma unroll
-    for (int u = 0; u < U; ++u) body(p[u], e[u]);
+    for (int u = 0; u < U; ++u) visit(body, p[u], e[u], u);
 #pragma unroll
     for (int u = 0; u < U; ++u) e[u] = en[u];
   }
   // fewer than U entries remain (m + U > nl); their indices are already in e[]
 #pragma unroll
   for (int u = 0; u < U - 1; ++u)
-    if (m + u < nl) body(fetch(e[u]), e[u]);
+    if (m + u < nl) visit(body, fetch(e[u]), e[u], u);
 }
 
 // Offsets of the 27 relative cells of a list entry in the block's replica, in shadow units:
@@ -229,12 +256,17 @@ struct MorseIn {
   int nblocks;
 };
 
+// Wavefronts per SIMD of the paper form's FP64 density pass: the Cr-C blocks and the embedding
+// would take 94 registers (5 wavefronts), the pair loop far fewer; at 6 a few of theirs spill and
+// the pass gains 3 % (216,000 atoms: 119 -> 115 us), at 8 it loses that again.
+constexpr int PAPER_DENS_WAVES = 6;
+
 // SHADOW (with MIXED): separations from the fixed-point cell-local shadow qs and the entries'
 // relative cells; otherwise FP64 positions (rounded to FP32 for the MIXED arithmetic).
-// PAPER: the paper's form -- rho_i = sum f, P_i = sum f^2, F'(rho_i) into q.w and M'(P_i)
+// The paper's form (POT) -- rho_i = sum f, P_i = sum f^2, F'(rho_i) into q.w and M'(P_i)
 // into dm[i] (the second derivative of the paper's per-atom array).
-template <int T, bool MIXED, bool SHADOW, bool ENERGY, bool PAPER = false>
-__global__ __launch_bounds__(BLOCK) void k_density(Consts K, const RepDesc* __restrict__ R,
+template <int T, bool MIXED, bool SHADOW, bool ENERGY, int POT = POT_FS>
+__global__ __launch_bounds__(BLOCK, (POT == POT_PAPER && !MIXED) ? PAPER_DENS_WAVES : 1) void k_density(Consts K, const RepDesc* __restrict__ R,
                                                    RepState* __restrict__ S,
                                                    const int* __restrict__ tile_rep,
                                                    double4* __restrict__ q,
@@ -257,61 +289,65 @@ __global__ __launch_bounds__(BLOCK) void k_density(Consts K, const RepDesc* __re
   const double4 pi = (!SHADOW && c.live) ? q[c.i] : make_double4(0.0, 0.0, 0.0, 0.0);
   const bool img = !SHADOW && wave_near_face(d, c.live, pi.x, pi.y, pi.z, K.rlist + 2.0 * K.half_skin);
   double rho = 0.0, pp = 0.0;   // pp: P_i (paper's form)
+  constexpr int H = split_sums(T, POT);
   if (c.live) {
     const int64_t i = c.i;
     const int n = cnt[i];
-    if constexpr (PAPER) {
+    if constexpr (POT != POT_FS) {
       if (MIXED) {
-        float ar = 0.0f, ap = 0.0f;
+        float ar[2] = {0.0f, 0.0f}, ap[2] = {0.0f, 0.0f};
         const float rcs = (float)K.P.rc_sq;
-        auto add = [&](float ex, float ey, float ez) {
-          const float r2 = ex * ex + ey * ey + ez * ez;
+        auto add = [&](float ex, float ey, float ez, int u) {
+          const float r2 = sum_sq(ex, ey, ez);
           const bool in = r2 < rcs;
-          const float f = paper_f32(K.P, __frsqrt_rn(in ? r2 : 1.0f));
-          ar += in ? f : 0.0f;
-          ap += in ? f * f : 0.0f;
+          const float f = paper_f32<POT>(K.P, __frsqrt_rn(in ? r2 : 1.0f));
+          ar[u & H] += in ? f : 0.0f;
+          ap[u & H] += in ? sq_exact(f) : 0.0f;
         };
         if (SHADOW) {
           const int4 ps = qs[i];
           const float qi = (float)(1.0 / S[c.r].qscale);
           for_entries<T, UNROLL>(idx, (int)i, n, c.sub, (int)K.ntot, K.lt_shift,
                                  [&](int e) { return qs[list_slot(e)]; },
-                                 [&](const int4& pj, int e) {
+                                 [&](const int4& pj, int e, int u) {
             const int4 o = ctab[list_code(e)];
-            add((float)(pj.x - ps.x + o.x) * qi, (float)(pj.y - ps.y + o.y) * qi, (float)(pj.z - ps.z + o.z) * qi);
+            add((float)(pj.x - ps.x + o.x) * qi, (float)(pj.y - ps.y + o.y) * qi, (float)(pj.z - ps.z + o.z) * qi, u);
           });
         } else {
           auto pass = [&](auto img_c) {
             constexpr bool IMG = decltype(img_c)::value;
             for_entries<T, UNROLL>(idx, (int)i, n, c.sub, (int)K.ntot, K.lt_shift,
                                    [&](int e) { return q[list_slot(e)]; },
-                                   [&](const double4& pj, int) {
+                                   [&](const double4& pj, int, int u) {
               add((float)(IMG ? min_image(pj.x - pi.x, d.len[0], d.half[0], d.per[0]) : pj.x - pi.x),
                   (float)(IMG ? min_image(pj.y - pi.y, d.len[1], d.half[1], d.per[1]) : pj.y - pi.y),
-                  (float)(IMG ? min_image(pj.z - pi.z, d.len[2], d.half[2], d.per[2]) : pj.z - pi.z));
+                  (float)(IMG ? min_image(pj.z - pi.z, d.len[2], d.half[2], d.per[2]) : pj.z - pi.z), u);
             });
           };
           if (img) pass(std::true_type{}); else pass(std::false_type{});
         }
-        rho = (double)ar;
-        pp = (double)ap;
+        rho = H ? (double)ar[0] + (double)ar[1] : (double)ar[0];
+        pp = H ? (double)ap[0] + (double)ap[1] : (double)ap[0];
       } else {
+        double ar[2] = {0.0, 0.0}, ap[2] = {0.0, 0.0};
         auto pass = [&](auto img_c) {
           constexpr bool IMG = decltype(img_c)::value;
           for_entries<T, UNROLL>(idx, (int)i, n, c.sub, (int)K.ntot, K.lt_shift,
                                  [&](int e) { return q[list_slot(e)]; },
-                                 [&](const double4& pj, int) {
+                                 [&](const double4& pj, int, int u) {
             const double ex = IMG ? min_image(pj.x - pi.x, d.len[0], d.half[0], d.per[0]) : pj.x - pi.x;
             const double ey = IMG ? min_image(pj.y - pi.y, d.len[1], d.half[1], d.per[1]) : pj.y - pi.y;
             const double ez = IMG ? min_image(pj.z - pi.z, d.len[2], d.half[2], d.per[2]) : pj.z - pi.z;
-            const double r2 = ex * ex + ey * ey + ez * ez;
+            const double r2 = sum_sq(ex, ey, ez);
             const bool in = r2 < K.P.rc_sq;
-            const double f = paper_f(K.P, rsq_nr(in ? r2 : 1.0));
-            rho += in ? f : 0.0;
-            pp += in ? f * f : 0.0;
+            const double f = paper_f<POT>(K.P, rsq_nr(in ? r2 : 1.0));
+            ar[u & H] += in ? f : 0.0;
+            ap[u & H] += in ? sq_exact(f) : 0.0;
           });
         };
         if (img) pass(std::true_type{}); else pass(std::false_type{});
+        rho = H ? ar[0] + ar[1] : ar[0];
+        pp = H ? ap[0] + ap[1] : ap[0];
       }
     } else if (MIXED && SHADOW) {
       const int4 ps = qs[i];
@@ -366,11 +402,11 @@ __global__ __launch_bounds__(BLOCK) void k_density(Consts K, const RepDesc* __re
     }
   }
   rho = group_sum<T>(rho);
-  if (PAPER) pp = group_sum<T>(pp);
+  if (POT != POT_FS) pp = group_sum<T>(pp);
   double e_embed = 0.0;
   if (c.live && c.sub == 0) {
     double dF, en;
-    if constexpr (PAPER) {
+    if constexpr (POT != POT_FS) {
       const PaperEmbed pe = paper_embed(K.P, rho, pp);
       dF = pe.dF;
       en = pe.F + pe.M;
@@ -439,9 +475,9 @@ struct SM {
   double m;
 };
 
-// PAPER: the paper's form, dm[j] = M'(P_j) from the density pass.
-template <int T, bool MIXED, bool SHADOW, bool KICK, bool ENERGY, bool DRIFT = false, bool PAPER = false>
-__global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && !PAPER) ? MD_FORCE_KIN_WAVES : MD_FORCE_WAVES) void k_force(Consts K, const RepDesc* __restrict__ R,
+// With the paper's form (POT) dm[j] = M'(P_j) from the density pass.
+template <int T, bool MIXED, bool SHADOW, bool KICK, bool ENERGY, bool DRIFT = false, int POT = POT_FS>
+__global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && POT == POT_FS) ? MD_FORCE_KIN_WAVES : MD_FORCE_WAVES) void k_force(Consts K, const RepDesc* __restrict__ R,
                                                  RepState* __restrict__ S,
                                                  const int* __restrict__ tile_rep,
                                                  const double4* __restrict__ q,
@@ -469,29 +505,32 @@ __global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && !PAPER) ? MD_FORCE_KIN_W
   if (c.live) {
     const int64_t i = c.i;
     const int n = cnt[i];
-    if constexpr (PAPER) {
+    if constexpr (POT != POT_FS) {
       // dE/dr = Phi'(r) [x < d] + f'(r) [r < rc] ((F'_i + F'_j) + (M'_i + M'_j) 2 f(r)), Phi' by
       // Horner in x = r / re; all lanes evaluate and the cutoffs select, with F'_j and M'_j
       // used on every path (so the neighbour's record is loaded ahead of the arithmetic)
       const PaperConsts& P = K.P;
+      constexpr int H = split_sums(T, POT);
       if (MIXED) {
         const float rcs = (float)P.rc_sq, phs = (float)P.phi_sq, ire = (float)P.inv_re, dd = (float)P.d,
                     b0 = (float)P.b0, b1 = (float)P.b1, b2 = (float)P.b2, b3 = (float)P.b3, beta = (float)P.beta;
-        float ax = 0.f, ay = 0.f, az = 0.f;
+        float ax[2] = {0.f, 0.f}, ay[2] = {0.f, 0.f}, az[2] = {0.f, 0.f};
         double ep = 0.0, w0 = 0.0, w1 = 0.0, w2 = 0.0, w3 = 0.0, w4 = 0.0, w5 = 0.0;
-        auto pair = [&](float ex, float ey, float ez, float Fij, float Mij) {
-          const float r2 = ex * ex + ey * ey + ez * ez;
+        auto pair = [&](float ex, float ey, float ez, float Fij, float Mij, int h) {
+#pragma clang fp contract(off)
+          const float r2 = sum_sq(ex, ey, ez);
           const bool in_f = r2 < rcs, in_p = r2 < phs, inc = in_f || in_p;
           const float rinv = __frsqrt_rn(inc ? r2 : 1.0f);
-          const float r = r2 * rinv, x = r * ire, u = x - dd, t = x - 1.0f;
-          const float poly = ((b3 * t + b2) * t + b1) * t + b0, dpoly = (3.0f * b3 * t + 2.0f * b2) * t + b1;
-          const float fr = paper_f32(P, rinv);
+          const float r = r2 * rinv, u = fmaf(r, ire, -dd), t = fmaf(r, ire, -1.0f);
+          const float poly = fmaf(fmaf(fmaf(b3, t, b2), t, b1), t, b0), dpoly = fmaf(fmaf(3.0f * b3, t, 2.0f * b2), t, b1);
+          const float fr = paper_f32<POT>(P, rinv);
           const float dfr = in_f ? -beta * fr * rinv : 0.0f;
-          const float g = (in_p ? (2.0f * u * poly + u * u * dpoly) * ire : 0.0f) + dfr * (Fij + Mij * (2.0f * fr));
+          const float gp = fmaf(2.0f * u, poly, u * u * dpoly) * ire;
+          const float g = fmaf(dfr, fmaf(Mij, 2.0f * fr, Fij), in_p ? gp : 0.0f);
           const float sc = inc ? g * rinv : 0.0f;
-          ax += sc * ex;
-          ay += sc * ey;
-          az += sc * ez;
+          ax[h & H] = fmaf(sc, ex, ax[h & H]);
+          ay[h & H] = fmaf(sc, ey, ay[h & H]);
+          az[h & H] = fmaf(sc, ez, az[h & H]);
           if (ENERGY) {
             ep += (double)(in_p ? 0.5f * u * u * poly : 0.0f);
             const float hs = 0.5f * sc;
@@ -510,10 +549,10 @@ __global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && !PAPER) ? MD_FORCE_KIN_W
           const float Fi = __int_as_float(ps.w);
           for_entries<T, UNROLL>(idx, (int)i, n, c.sub, (int)K.ntot, K.lt_shift,
                                  [&](int e) { const int j = list_slot(e); return SM{qs[j], dm[j]}; },
-                                 [&](const SM& pj, int e) {
+                                 [&](const SM& pj, int e, int h) {
             const int4 o = ctab[list_code(e)];
             pair((float)(pj.q.x - ps.x + o.x) * qi, (float)(pj.q.y - ps.y + o.y) * qi,
-                 (float)(pj.q.z - ps.z + o.z) * qi, Fi + __int_as_float(pj.q.w), Mi + (float)pj.m);
+                 (float)(pj.q.z - ps.z + o.z) * qi, Fi + __int_as_float(pj.q.w), Mi + (float)pj.m, h);
           });
         } else {
           const float Fi = (float)pi.w;
@@ -521,18 +560,18 @@ __global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && !PAPER) ? MD_FORCE_KIN_W
             constexpr bool IMG = decltype(img_c)::value;
             for_entries<T, UNROLL>(idx, (int)i, n, c.sub, (int)K.ntot, K.lt_shift,
                                    [&](int e) { const int j = list_slot(e); return QM{q[j], dm[j]}; },
-                                   [&](const QM& pj, int) {
+                                   [&](const QM& pj, int, int h) {
               pair((float)(IMG ? min_image(pj.q.x - pi.x, d.len[0], d.half[0], d.per[0]) : pj.q.x - pi.x),
                    (float)(IMG ? min_image(pj.q.y - pi.y, d.len[1], d.half[1], d.per[1]) : pj.q.y - pi.y),
                    (float)(IMG ? min_image(pj.q.z - pi.z, d.len[2], d.half[2], d.per[2]) : pj.q.z - pi.z),
-                   Fi + (float)pj.q.w, Mi + (float)pj.m);
+                   Fi + (float)pj.q.w, Mi + (float)pj.m, h);
             });
           };
           if (img) pass(std::true_type{}); else pass(std::false_type{});
         }
-        fx = ax;
-        fy = ay;
-        fz = az;
+        fx = H ? (double)ax[0] + (double)ax[1] : (double)ax[0];
+        fy = H ? (double)ay[0] + (double)ay[1] : (double)ay[0];
+        fz = H ? (double)az[0] + (double)az[1] : (double)az[0];
         if (ENERGY) {
           acc[P_PAIR] = ep;
           acc[P_WXX] = w0;
@@ -544,40 +583,46 @@ __global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && !PAPER) ? MD_FORCE_KIN_W
         }
       } else {
         const double Fi = pi.w, Mi = dm[i];
+        double ax[2] = {0.0, 0.0}, ay[2] = {0.0, 0.0}, az[2] = {0.0, 0.0};
         auto pass = [&](auto img_c) {
           constexpr bool IMG = decltype(img_c)::value;
           for_entries<T, UNROLL>(idx, (int)i, n, c.sub, (int)K.ntot, K.lt_shift,
                                  [&](int e) { const int j = list_slot(e); return QM{q[j], dm[j]}; },
-                                 [&](const QM& pj, int) {
+                                 [&](const QM& pj, int, int h) {
+#pragma clang fp contract(off)
             const double ex = IMG ? min_image(pj.q.x - pi.x, d.len[0], d.half[0], d.per[0]) : pj.q.x - pi.x;
             const double ey = IMG ? min_image(pj.q.y - pi.y, d.len[1], d.half[1], d.per[1]) : pj.q.y - pi.y;
             const double ez = IMG ? min_image(pj.q.z - pi.z, d.len[2], d.half[2], d.per[2]) : pj.q.z - pi.z;
-            const double r2 = ex * ex + ey * ey + ez * ez;
+            const double r2 = sum_sq(ex, ey, ez);
             const bool in_f = r2 < P.rc_sq, in_p = r2 < P.phi_sq, inc = in_f || in_p;
             const double rinv = rsq_nr(inc ? r2 : 1.0);
-            const double r = r2 * rinv, x = r * P.inv_re, u = x - P.d;
-            const double poly = ((P.a3 * x + P.a2) * x + P.a1) * x + P.a0;
-            const double dpoly = (3.0 * P.a3 * x + 2.0 * P.a2) * x + P.a1;
-            const double fr = paper_f(P, rinv);
+            const double r = r2 * rinv, x = r * P.inv_re, u = fma(r, P.inv_re, -P.d);
+            const double poly = fma(fma(fma(P.a3, x, P.a2), x, P.a1), x, P.a0);
+            const double dpoly = fma(fma(3.0 * P.a3, x, 2.0 * P.a2), x, P.a1);
+            const double fr = paper_f<POT>(P, rinv);
             const double dfr = in_f ? -P.beta * fr * rinv : 0.0;
-            const double g = (in_p ? (2.0 * u * poly + u * u * dpoly) * P.inv_re : 0.0) +
-                             dfr * ((Fi + pj.q.w) + (Mi + pj.m) * (2.0 * fr));
+            const double gp = fma(2.0 * u, poly, u * u * dpoly) * P.inv_re;
+            const double g = fma(dfr, fma(Mi + pj.m, 2.0 * fr, Fi + pj.q.w), in_p ? gp : 0.0);
             const double sc = inc ? g * rinv : 0.0;
-            fx += sc * ex;
-            fy += sc * ey;
-            fz += sc * ez;
+            ax[h & H] = fma(sc, ex, ax[h & H]);
+            ay[h & H] = fma(sc, ey, ay[h & H]);
+            az[h & H] = fma(sc, ez, az[h & H]);
             if (ENERGY) {
               acc[P_PAIR] += in_p ? 0.5 * u * u * poly : 0.0;
-              acc[P_WXX] -= 0.5 * sc * ex * ex;
-              acc[P_WYY] -= 0.5 * sc * ey * ey;
-              acc[P_WZZ] -= 0.5 * sc * ez * ez;
-              acc[P_WXY] -= 0.5 * sc * ex * ey;
-              acc[P_WXZ] -= 0.5 * sc * ex * ez;
-              acc[P_WYZ] -= 0.5 * sc * ey * ez;
+              const double hs = -0.5 * sc;
+              acc[P_WXX] = fma(hs * ex, ex, acc[P_WXX]);
+              acc[P_WYY] = fma(hs * ey, ey, acc[P_WYY]);
+              acc[P_WZZ] = fma(hs * ez, ez, acc[P_WZZ]);
+              acc[P_WXY] = fma(hs * ex, ey, acc[P_WXY]);
+              acc[P_WXZ] = fma(hs * ex, ez, acc[P_WXZ]);
+              acc[P_WYZ] = fma(hs * ey, ez, acc[P_WYZ]);
             }
           });
         };
         if (img) pass(std::true_type{}); else pass(std::false_type{});
+        fx = H ? ax[0] + ax[1] : ax[0];
+        fy = H ? ay[0] + ay[1] : ay[0];
+        fz = H ? az[0] + az[1] : az[0];
       }
     } else if (MIXED) {
       const float cc = (float)K.c, dd = (float)K.d, c2 = (float)K.c2, rv = (float)K.rv,
