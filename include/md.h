@@ -219,7 +219,8 @@ MD_API int64_t md_system_carbons(const md_system *sys);
 MD_API int64_t md_replica_offset(const md_system *sys, int32_t r);
 
 /* Bytes of device workspace the system needs (cell grids, sort buffers, reference
- * positions, flags, reduction partials). */
+ * positions, flags, reduction partials; with two-tier lists the middle lists, which speed up
+ * the inner lists' refill). */
 MD_API size_t md_workspace_bytes(const md_system *sys);
 
 /* Bind a caller-owned device workspace of at least md_workspace_bytes bytes: writes the
@@ -236,7 +237,9 @@ MD_API int md_workspace_bind(md_system *sys, void *ws, size_t bytes, void *strea
  * list arrays are still the caller's).  The array lives on every GPU the library runs on
  * (each GPU its own copy, at its own address, looked up at the first such call on that GPU,
  * which must be current) until the process ends.  MD_ERR_ARG, with a message on stderr, when
- * md_workspace_bytes(sys) exceeds MD_SCRATCH_BYTES (about 60,000 atoms).
+ * md_workspace_bytes(sys) exceeds MD_SCRATCH_BYTES (about 60,000 atoms).  Two-tier lists' middle
+ * lists do not count towards that: where they do not fit, the inner lists are refilled from the
+ * outer ones, with the same results.
  * One scratch per GPU: binding a system takes it over, clears it and keeps nothing of the
  * previous system; calls on a system bound to it earlier then return MD_ERR_STATE (bind that
  * system again to use it).  Calls on one GPU whose work overlaps on the device (several

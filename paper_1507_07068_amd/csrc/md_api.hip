@@ -26,7 +26,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 struct Layout {
   size_t desc, state, tile_rep, c_rep, misc, bk_rep, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
       tf, tfixed, tid, count, start, hcell, hrank, hlist, hsorted, scan_state, hnear, near, fme, p_embed, p_force,
-      p_morse, p_kin, dm, dmax_p, tbox_p, total;
+      p_morse, p_kin, dm, dmax_p, tbox_p, base, midx, mcnt, mref, total;
 };
 
 constexpr int MISC_INTS = 16;    // rebuild flag, status words
@@ -35,6 +35,10 @@ constexpr int MISC_INTS = 16;    // rebuild flag, status words
 // atoms.  60 steps of a film, 8 against 4 lanes: 12,800 atoms 0.84 of the time, 41,000 0.97,
 // 52,000 the same, 80,000 1.05, 175,000 1.10.
 constexpr int64_t LANES8_ATOMS = 49152;
+// Two-tier lists: the middle lists' radius is r* (1 + MID_SKIN), 0.66 A of skin in the paper's
+// form.  They are taken again, at four times a refill, when an atom has moved half of that; 0.12
+// made each refill 7 % dearer, 0.05 no cheaper (the same lattice shells).
+constexpr double MID_SKIN = 0.08;
 constexpr int SCAN_CHUNK = 2048; // cells per block of the cell-count scan
 constexpr int64_t DECIDE_IN_BIN_MAX_LOADS = (int64_t)1 << 22;   // part loads over all k_bin blocks
 constexpr int PARTS_REDUCED = 64;   // partial reductions of a large single replica's parts
@@ -58,6 +62,8 @@ struct md_system {
   Layout L;
   char* ws;
   int scan_blocks;
+  int mid_cap = 0;        // two-tier lists: capacity of the middle lists
+  bool mid = false;       // the bound workspace holds them
   bool list_mix;   // some periodic axis has fewer than 3 list cells
   bool have_embed, have_force;
   // md_run's energy steps other than the last take the kinetic energy inside the force pass
@@ -153,7 +159,12 @@ Layout make_layout(const md_system& s) {
   // k_kinetic's partials per tile, or those of a force pass that takes them (per block)
   L.p_morse = take(sizeof(double) * nt * s.K.ln * 4);
   L.p_kin = take(sizeof(double) * nt * s.K.ln);
-  L.total = o;
+  L.base = o;
+  // the middle lists of two-tier lists (a workspace without them serves too: see MidList)
+  L.midx = take(s.p.icap ? sizeof(int) * n * (size_t)s.mid_cap : 0);
+  L.mcnt = take(s.p.icap ? sizeof(int) * n : 0);
+  L.mref = take(s.p.icap ? sizeof(float) * 4 * n : 0);
+  L.total = s.p.icap ? o : L.base;
   return L;
 }
 
@@ -497,6 +508,12 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   K.cap = p->cap;
   K.xcap = p->xcap;
   K.icap = p->icap;
+  K.mid_skin = MID_SKIN * cut;
+  K.mid_rc_sq = (cut + K.mid_skin) * (cut + K.mid_skin);
+  if (p->icap) {   // the inner capacity times the volume, a whole number of interleaved groups
+    const double g = (1.0 + MID_SKIN) * (1.0 + MID_SKIN) * (1.0 + MID_SKIN);
+    s->mid_cap = std::min(p->cap, (int)((std::ceil(p->icap * g) + 7.0) / 8.0) * 8);
+  }
   K.nrep = nrep;
   K.lt = p->tpa;
   K.lt_shift = p->tpa == 1 ? 0 : (p->tpa == 2 ? 1 : (p->tpa == 4 ? 2 : 3));
@@ -551,10 +568,11 @@ MD_API size_t md_workspace_bytes(const md_system* s) { return s ? s->L.total : 0
 namespace {
 
 // Takes ws as the workspace of s: cleared, descriptors written, stream synchronised.
-int bind_workspace(md_system* s, void* ws, hipStream_t st) {
+int bind_workspace(md_system* s, void* ws, size_t bytes, hipStream_t st) {
   s->ws = (char*)ws;
+  s->mid = s->p.icap && bytes >= s->L.total;
   int e;
-  if ((e = hip_status(hipMemsetAsync(ws, 0, s->L.total, st)))) return e;
+  if ((e = hip_status(hipMemsetAsync(ws, 0, s->L.base, st)))) return e;
   if ((e = hip_status(hipMemcpyAsync(at<RepDesc>(s, s->L.desc), s->desc.data(),
                                      sizeof(RepDesc) * s->nrep, hipMemcpyHostToDevice, st))))
     return e;
@@ -591,16 +609,16 @@ MD_API int md_workspace_bind(md_system* s, void* ws, size_t bytes, void* stream)
     g_scratch_owner[s->static_dev].compare_exchange_strong(me, nullptr);
     s->static_dev = -1;
   }
-  return bind_workspace(s, ws, (hipStream_t)stream);
+  return bind_workspace(s, ws, bytes, (hipStream_t)stream);
 }
 
 MD_API int md_workspace_bind_static(md_system* s, void* stream) {
   if (!s) return MD_ERR_ARG;
-  if (s->L.total > (size_t)MD_SCRATCH_BYTES) {
+  if (s->L.base > (size_t)MD_SCRATCH_BYTES) {
     std::fprintf(stderr,
                  "md_workspace_bind_static: this system needs %zu bytes of workspace, more than the "
                  "%d bytes of the static scratch; bind a caller-owned workspace with md_workspace_bind\n",
-                 s->L.total, (int)MD_SCRATCH_BYTES);
+                 s->L.base, (int)MD_SCRATCH_BYTES);
     return MD_ERR_ARG;
   }
   int dev = 0, e;
@@ -619,7 +637,7 @@ MD_API int md_workspace_bind_static(md_system* s, void* stream) {
     g_scratch_owner[dev].store(s);   // earlier systems bound to it are now refused
   }
   s->static_dev = dev;
-  return bind_workspace(s, ptr, (hipStream_t)stream);
+  return bind_workspace(s, ptr, MD_SCRATCH_BYTES, (hipStream_t)stream);
 }
 
 namespace {
@@ -741,11 +759,16 @@ namespace {
 // Two-tier lists: the inner list refilled from the outer one at the current positions.
 int inner_list(md_system* s, const md_atoms* a, const md_lists* l, hipStream_t st) {
   if (!s->p.icap) return MD_OK;
-  k_inner_pos<<<grid_tiles(s), BLOCK, 0, st>>>(at<RepDesc>(s, s->L.desc), at<RepState>(s, s->L.state),
-                                               at<int>(s, s->L.tile_rep), qcur(s, a), at<float4>(s, s->L.tqf));
-  k_inner_list<<<grid_tiles(s) * INNER_G, BLOCK, 0, st>>>(s->K, at<RepDesc>(s, s->L.desc), at<RepState>(s, s->L.state),
-                                                at<int>(s, s->L.tile_rep), qcur(s, a), at<float4>(s, s->L.tqf),
-                                                l->idx, l->cnt, l->iidx, l->icnt);
+  const RepDesc* R = at<RepDesc>(s, s->L.desc);
+  RepState* S = at<RepState>(s, s->L.state);
+  const int* tr = at<int>(s, s->L.tile_rep);
+  const double4* q = qcur(s, a);
+  float4* qf = at<float4>(s, s->L.tqf);
+  const MidList M{s->mid ? at<int>(s, s->L.midx) : nullptr, at<int>(s, s->L.mcnt), at<float4>(s, s->L.mref), s->mid_cap};
+  const int nm = grid_tiles(s) * MID_G;
+  k_inner_pos<<<grid_tiles(s), BLOCK, 0, st>>>(s->K, R, S, tr, q, qf, M);
+  if (s->mid) k_mid_list<<<std::min(nm, 4 * s->tile_grid), BLOCK, 0, st>>>(s->K, R, S, tr, q, qf, l->idx, l->cnt, M, nm);
+  k_inner_list<<<grid_tiles(s) * INNER_G, BLOCK, 0, st>>>(s->K, R, S, tr, q, qf, l->idx, l->cnt, M, l->iidx, l->icnt);
   return check_launch();
 }
 

@@ -47,6 +47,7 @@ struct alignas(64) RepState {
   int nnear;              // Cr atoms within reach of the carbons (entries of the near list)
   int nnear_old;          // entries of the previous build's near list (during a rebuild)
   int ioverflow;          // needed inner-list capacity (two-tier lists; 0 = fits)
+  int mid_ok;             // two-tier lists: the middle list holds at the current positions
   // Cr cell grid of the current build: origin, cells per Angstrom, dims (<= gcap).  Along
   // periodic axes it is the box; along open axes it spans the atoms' current extent.
   double glo[3], ginv[3];
@@ -185,6 +186,8 @@ struct Consts {
   double icut_sq;         // two-tier lists: the inner list's radius (the largest Cr-Cr cutoff), squared
   int cap, xcap;
   int icap;               // two-tier lists: inner-list capacity (0: one list)
+  double mid_skin;        // two-tier lists: the middle list's radius is the inner list's plus this
+  double mid_rc_sq;       // (that radius squared)
   int nrep;
   int lt;                 // list interleave: entries k..k+lt-1 of an atom are adjacent
   int lt_shift;           // log2(lt)

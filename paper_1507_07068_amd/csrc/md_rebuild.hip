@@ -179,6 +179,7 @@ __device__ __forceinline__ void record_grid(const Consts& K, const RepDesc& d, R
   s.rebuild = g.need;
   if (!g.need) return;
   choose_bricks(d.n, d.bcap, g.gd, s.bn);
+  s.mid_ok = 0;
   s.nnear_old = s.nnear;
   s.nnear = 0;
   for (int a = 0; a < 3; ++a) {
@@ -1205,31 +1206,65 @@ __global__ __launch_bounds__(BLOCK) void k_xlist(Consts K, BuildArgs A) {
   xlist_pass<BLOCK>(K, A, cand_sh, pre, blockIdx.x, gridDim.x);
 }
 
-// Section 2.6's inner list, refilled every step from the outer (Verlet) list: atom i's outer
-// entries whose pair is closer than the largest Cr-Cr cutoff at the current positions
-// (minimum image, the list build's exact FP64 predicate), in their outer-list order and in
-// the outer list's layout and entry format.  INNER_G lanes share an atom and test INNER_G
-// consecutive outer entries at a time (the next ones' indices loaded while the current
-// positions are gathered); a ballot over the group gives each kept entry its place, so the
-// order is the outer list's.  One block per 256 / INNER_G atoms.
-#ifndef MD_INNER_G
-#define MD_INNER_G 16   // 4: 978 us on the 216k-atom film (paper's form); 8: 823; 16: 790
-#endif
-constexpr int INNER_G = MD_INNER_G;
+// Section 2.6's inner list, refilled every step: atom i's outer (Verlet) entries whose pair is
+// closer than the largest Cr-Cr cutoff r* at the current positions (minimum image, the list
+// build's exact FP64 predicate), in their outer-list order and in the outer list's layout and
+// entry format.  INNER_G lanes share an atom and test INNER_G consecutive entries at a time (the
+// next ones' indices loaded while the current positions are gathered); a ballot over the group
+// gives each kept entry its place, so the order is the source list's.
+//
+// The source is a middle list: the outer entries closer than r* + mid_skin at the positions mref,
+// taken again (k_mid_list) when an atom of the replica has moved more than mid_skin / 2 from
+// there, or the outer list is new.  Every pair within r* is then in it, as every pair within r*
+// is in the outer list, so the inner list is the one that the outer list itself gives.  What
+// bounds the refill is the gather of one position per source entry: the paper's form has about
+// 940 outer entries an atom and 260 middle ones.  On the 216k-atom film the refill from the outer
+// list took 787 us a step, from the middle one 222 (4 lanes an atom 231, 16 262), and the middle
+// list itself takes 940.
+constexpr int INNER_G = 8;
+constexpr int MID_G = 16;
+
+// The middle list (idx null: the workspace holds none, and the outer list is the source).
+struct MidList {
+  int* idx;       // [cap][ntot], laid out as the outer list
+  int* cnt;       // [ntot]; < 0: more entries than cap, and the outer list is this atom's source
+  float4* ref;    // [ntot] the positions (as k_inner_pos gives them) it was taken at
+  int cap;
+};
+
+// Bound on the error of an FP32 position relative to the grid origin, per axis, for atoms within
+// R of the grid, images included (the list build's).
+__device__ __forceinline__ double pos_err(const RepDesc& d, const RepState& s, int a, double R) {
+  const double E = s.gd[a] / s.ginv[a] + 2.0 * R;
+  return 0x1p-24 * (3.0 * E + (d.per[a] ? 2.0 * d.len[a] : 0.0) + 3.0 * R);
+}
 
 // FP32 positions relative to the replica's grid origin at the current positions, for the
 // inner-list screen (one lane per atom slot; the list build's scratch copy, free between
-// builds).
-__global__ __launch_bounds__(BLOCK) void k_inner_pos(const RepDesc* __restrict__ R, const RepState* __restrict__ S,
+// builds); an atom that has moved too far from the middle list's reference marks that list.
+__global__ __launch_bounds__(BLOCK) void k_inner_pos(Consts K, const RepDesc* __restrict__ R, RepState* __restrict__ S,
                                                      const int* __restrict__ tile_rep, const double4* __restrict__ q,
-                                                     float4* __restrict__ qf) {
+                                                     float4* __restrict__ qf, MidList M) {
   static_assert(TILE == BLOCK, "one block per tile");
   const int r = tile_rep[blockIdx.x];
+  const RepDesc& d = R[r];
   const int64_t i = (int64_t)blockIdx.x * TILE + threadIdx.x;
-  if (i >= (int64_t)R[r].a0 + R[r].n) return;
+  if (i >= (int64_t)d.a0 + d.n) return;
   const double4 p = q[i];
-  const RepState& s = S[r];
-  qf[i] = make_float4((float)(p.x - s.glo[0]), (float)(p.y - s.glo[1]), (float)(p.z - s.glo[2]), 0.0f);
+  RepState& s = S[r];
+  const float4 f = make_float4((float)(p.x - s.glo[0]), (float)(p.y - s.glo[1]), (float)(p.z - s.glo[2]), 0.0f);
+  qf[i] = f;
+  if (M.idx) {
+    const float4 o = M.ref[i];
+    const double R0 = K.rlist + 1.0;
+    double err = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) err += 2.0 * pos_err(d, s, a, R0);
+    const float th = (float)(0.5 * K.mid_skin * 0.999 - err);
+    const float dx = f.x - o.x, dy = f.y - o.y, dz = f.z - o.z;
+    const bool still = th > 0.0f && dx * dx + dy * dy + dz * dz <= th * th;   // (a NaN is not)
+    if (!still) s.mid_ok = 0;
+  }
 }
 
 __device__ __forceinline__ float min_image_f(float d, float len, float half, int per) {
@@ -1238,30 +1273,36 @@ __device__ __forceinline__ float min_image_f(float d, float len, float half, int
   return d + s;
 }
 
-// The screen: the FP32 squared separation from those positions decides outside a band
-// around r*^2 that covers its error (the list build's bound, with R = r* + 1 and positions
-// within R of the grid); the band gets the exact FP64 test.  On a replica with a periodic
-// length under 2 R + 1 the FP32 minimum image could pick the other image of a pair inside
-// r*, and every entry gets the exact test.
-__global__ __launch_bounds__(BLOCK) void k_inner_list(Consts K, const RepDesc* __restrict__ R,
-                                                      RepState* __restrict__ S, const int* __restrict__ tile_rep,
-                                                      const double4* __restrict__ q, const float4* __restrict__ qf,
-                                                      const int* __restrict__ idx, const int* __restrict__ cnt,
-                                                      int* __restrict__ iidx, int* __restrict__ icnt) {
-  static_assert(WAVE % INNER_G == 0 && INNER_G < 32, "a lane group lies in one wavefront, its mask in 32 bits");
-  constexpr int APB = BLOCK / INNER_G;   // atoms per block
-  const int lb = xcd_block(blockIdx.x, gridDim.x);
-  const int tile = lb / INNER_G;
-  const int r = tile_rep[tile];
-  const RepDesc& d = R[r];
-  const int sub = threadIdx.x % INNER_G;
-  const int64_t i = (int64_t)tile * TILE + (lb % INNER_G) * APB + threadIdx.x / INNER_G;
+// Entries of a list that are closer than sqrt(rc2), G lanes per atom, for the atoms of one
+// 256 / G-atom block `lb`.  The FP32 squared separation decides outside a band around rc2
+// that covers its error (the list build's bound, with R = sqrt(rc2) + 1 and positions within R
+// of the grid); the band gets the exact FP64 test or, with MID, is kept.  On a replica with a
+// periodic length under 2 R + 1 the FP32 minimum image could pick the other image of a pair
+// inside the radius, and every entry lies in the band.  MID: the middle list from the outer one;
+// else the inner list from the middle one (from the outer one where that has none).
+template <int G, bool MID>
+__device__ __forceinline__ void filter_list(const Consts& K, const RepDesc& d, RepState& s, int tile, int lb,
+                                            const double4* __restrict__ q, const float4* __restrict__ qf,
+                                            const int* __restrict__ idx, const int* __restrict__ cnt, const MidList& M,
+                                            int* __restrict__ oidx, int* __restrict__ ocnt, int ocap, double rc2) {
+  static_assert(WAVE % G == 0 && G < 32, "a lane group lies in one wavefront, its mask in 32 bits");
+  constexpr int APB = BLOCK / G;   // atoms per block
+  const int sub = threadIdx.x % G;
+  const int64_t i = (int64_t)tile * TILE + (lb % G) * APB + threadIdx.x / G;
   const bool live = i < (int64_t)d.a0 + d.n;
   const double4 pi = live ? q[i] : make_double4(0.0, 0.0, 0.0, 0.0);
   const float4 pif = live ? qf[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   const bool img = wave_near_face(d, live, pi.x, pi.y, pi.z, K.rlist + 2.0 * K.half_skin);
   // every lane takes part in the ballots (atoms past the replica with an empty list)
-  const int n = live ? cnt[i] : 0;
+  const int* src = idx;
+  int n = 0;
+  if (!MID && M.idx) {
+    n = live ? M.cnt[i] : 0;
+    if (n >= 0) src = M.idx;
+    else n = cnt[i];
+  } else {
+    n = live ? cnt[i] : 0;
+  }
   int nw = n;   // the wavefront's longest list
 #pragma unroll
   for (int o = WAVE / 2; o > 0; o >>= 1) nw = max(nw, __shfl_xor(nw, o, WAVE));
@@ -1269,18 +1310,14 @@ __global__ __launch_bounds__(BLOCK) void k_inner_list(Consts K, const RepDesc* _
   const unsigned stride = (unsigned)K.ntot * T, base = (unsigned)(live ? i : 0) * T;
   // word offset of entry k of atom i (32-bit: the lists hold fewer than 2^31 words)
   auto at_k = [&](int k) { return ((unsigned)k >> sh) * stride + base + (unsigned)(k & (T - 1)); };
-  const int icap = K.icap;
-  const double rc2 = K.icut_sq;
   float lo_f = -1.0f, hi_f = INFINITY;   // (everything in the band)
   {
-    const RepState& s = S[r];
     const double u = 0x1p-24, Rr = sqrt(rc2) + 1.0;
     double err = 4.0 * u * (rc2 + Rr * Rr);
     bool ok = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double E = s.gd[a] / s.ginv[a] + 2.0 * Rr;
-      const double eta = u * (3.0 * E + (d.per[a] ? 2.0 * d.len[a] : 0.0) + 3.0 * Rr);
+      const double eta = pos_err(d, s, a, Rr);
       err += 2.0 * Rr * eta + eta * eta;
       ok = ok && !(d.per[a] && d.len[a] <= 2.0 * Rr + 1.0);
     }
@@ -1295,11 +1332,11 @@ __global__ __launch_bounds__(BLOCK) void k_inner_list(Consts K, const RepDesc* _
   const int gshift = (int)(threadIdx.x % WAVE) - sub;   // the group's first lane
   const unsigned below = (1u << sub) - 1u;
   int c = 0;        // entries kept so far
-  int e = sub < n ? idx[at_k(sub)] : 0;   // (slot 0 stands in for an entry past the list)
-  for (int m0 = 0; m0 < nw; m0 += INNER_G) {
+  int e = sub < n ? src[at_k(sub)] : 0;   // (slot 0 stands in for an entry past the list)
+  for (int m0 = 0; m0 < nw; m0 += G) {
     const int k = m0 + sub;
     const float4 pjf = qf[list_slot(e)];
-    const int en = k + INNER_G < n ? idx[at_k(k + INNER_G)] : 0;
+    const int en = k + G < n ? src[at_k(k + G)] : 0;
     float fx = pjf.x - pif.x, fy = pjf.y - pif.y, fz = pjf.z - pif.z;
     if (img) {
       fx = min_image_f(fx, len0, hf0, d.per[0]);
@@ -1307,30 +1344,65 @@ __global__ __launch_bounds__(BLOCK) void k_inner_list(Consts K, const RepDesc* _
       fz = min_image_f(fz, len2, hf2, d.per[2]);
     }
     const float r2f = fx * fx + fy * fy + fz * fz;
-    bool keep = r2f < lo_f;
-    if (k < n && !keep && !(r2f >= hi_f)) {   // the band (or NaN): the exact test
-      const double4 pj = q[list_slot(e)];
-      double ex = pj.x - pi.x, ey = pj.y - pi.y, ez = pj.z - pi.z;
-      if (img) {
-        ex = min_image(ex, d.len[0], d.half[0], d.per[0]);
-        ey = min_image(ey, d.len[1], d.half[1], d.per[1]);
-        ez = min_image(ez, d.len[2], d.half[2], d.per[2]);
+    bool keep;
+    if (MID) {
+      keep = !(r2f >= hi_f);   // (NaN: kept)
+    } else {
+      keep = r2f < lo_f;
+      if (k < n && !keep && !(r2f >= hi_f)) {   // the band (or NaN): the exact test
+        const double4 pj = q[list_slot(e)];
+        double ex = pj.x - pi.x, ey = pj.y - pi.y, ez = pj.z - pi.z;
+        if (img) {
+          ex = min_image(ex, d.len[0], d.half[0], d.per[0]);
+          ey = min_image(ey, d.len[1], d.half[1], d.per[1]);
+          ez = min_image(ez, d.len[2], d.half[2], d.per[2]);
+        }
+        keep = dist_sq_exact(ex, ey, ez) < rc2;
       }
-      keep = dist_sq_exact(ex, ey, ez) < rc2;
     }
     keep = keep && k < n;
-    const unsigned gm = (unsigned)(__ballot(keep) >> gshift) & ((1u << INNER_G) - 1u);
+    const unsigned gm = (unsigned)(__ballot(keep) >> gshift) & ((1u << G) - 1u);
     if (keep) {
       const int j = c + __popc(gm & below);
-      if (j < icap) iidx[at_k(j)] = e;
+      if (j < ocap) oidx[at_k(j)] = e;
     }
     c += __popc(gm);
     e = en;
   }
   if (live && sub == 0) {
-    icnt[i] = min(c, icap);
-    if (c > icap) atomicMax(&S[r].ioverflow, c);
+    if (MID) {
+      ocnt[i] = c > ocap ? -1 : c;
+      M.ref[i] = pif;
+    } else {
+      ocnt[i] = min(c, ocap);
+      if (c > ocap) atomicMax(&s.ioverflow, c);
+    }
   }
+}
+
+// The middle lists of the replicas whose own no longer holds (blocks stride over the tiles, as
+// most launches have none).
+__global__ __launch_bounds__(BLOCK) void k_mid_list(Consts K, const RepDesc* __restrict__ R, RepState* __restrict__ S,
+                                                    const int* __restrict__ tile_rep, const double4* __restrict__ q,
+                                                    const float4* __restrict__ qf, const int* __restrict__ idx,
+                                                    const int* __restrict__ cnt, MidList M, int nb) {
+  for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+    const int lb = xcd_block(b, nb), tile = lb / MID_G, r = tile_rep[tile];
+    if (S[r].mid_ok) continue;   // (uniform over the block)
+    filter_list<MID_G, true>(K, R[r], S[r], tile, lb, q, qf, idx, cnt, M, M.idx, M.cnt, M.cap, K.mid_rc_sq);
+  }
+}
+
+// One block per 256 / INNER_G atoms.
+__global__ __launch_bounds__(BLOCK) void k_inner_list(Consts K, const RepDesc* __restrict__ R,
+                                                      RepState* __restrict__ S, const int* __restrict__ tile_rep,
+                                                      const double4* __restrict__ q, const float4* __restrict__ qf,
+                                                      const int* __restrict__ idx, const int* __restrict__ cnt,
+                                                      MidList M, int* __restrict__ iidx, int* __restrict__ icnt) {
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int tile = lb / INNER_G, r = tile_rep[tile];
+  if (M.idx && lb % INNER_G == 0 && tile == R[r].t0 && threadIdx.x == 0) S[r].mid_ok = 1;   // (nothing here reads it)
+  filter_list<INNER_G, false>(K, R[r], S[r], tile, lb, q, qf, idx, cnt, M, iidx, icnt, K.icap, K.icut_sq);
 }
 
 }  // namespace md
