@@ -24,7 +24,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Byte offsets of the workspace regions.
 struct Layout {
-  size_t desc, state, tile_rep, c_rep, misc, bk_rep, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
+  size_t desc, state, tile_rep, c_rep, misc, sync, bk_rep, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
       tf, tfixed, tid, count, start, hcell, hrank, hlist, hsorted, scan_state, hnear, near, fme, p_embed, p_force,
       p_morse, p_kin, dm, dmax_p, tbox_p, base, midx, mcnt, mref, total;
 };
@@ -122,6 +122,7 @@ Layout make_layout(const md_system& s) {
   L.bk_rep = take(s.nrep > 1 ? sizeof(int) * (size_t)s.bcap : 0);
   L.c_rep = take(sizeof(int) * (size_t)s.ctot);
   L.misc = take(sizeof(int) * MISC_INTS);
+  L.sync = take(sizeof(int) * SYNC_INTS);
   L.chunks = take(sizeof(int2) * s.chunks.size());
   L.chunk_out = take(sizeof(double) * 16 * s.chunks.size());
   L.xref = take(sizeof(double) * 3 * n);
@@ -688,6 +689,7 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   A.hsorted = at<double4>(s, s->L.hsorted);
   A.scan_state = at<long long>(s, s->L.scan_state);
   A.scan_ticket = misc + 1;
+  A.sync = at<int>(s, s->L.sync);
   A.idx = l->idx;
   A.cnt = l->cnt;
   A.xidx = l->xidx;
@@ -713,7 +715,11 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   const int64_t bin_blocks = tgrid, nparts = (int64_t)s->ntiles * s->ppt;
   const bool decide_in_bin = !(flags & MD_B_FORCE) && s->K.nrep == 1;
   A.commit_ref = decide_in_bin ? 1 : 0;
-  if (decide_in_bin && bin_blocks * nparts <= DECIDE_IN_BIN_MAX_LOADS) {
+  const bool fused = A.nbin <= REBUILD_ITEMS;   // (then the parts are few too)
+  if (fused && decide_in_bin) {
+    k_rebuild<true><<<tgrid, BLOCK, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
+                                             (int)nparts);
+  } else if (decide_in_bin && bin_blocks * nparts <= DECIDE_IN_BIN_MAX_LOADS) {
     k_bin<true><<<tgrid, BLOCK, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
                                          (int)nparts);
   } else if (decide_in_bin) {
@@ -727,11 +733,16 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
       k_tile_box<<<s->ntiles, BLOCK, 0, st>>>(A.R, A.tile_rep, A.q, at<double>(s, s->L.tbox));
     k_decide<<<1, DECIDE_THREADS, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
                                   (flags & MD_B_FORCE) ? 1 : 0, (flags & MD_B_FORCE) ? 1 : s->ppt);
-    k_bin<false><<<tgrid, BLOCK, 0, st>>>(s->K, A, nullptr, nullptr, 0);
+    if (fused)
+      k_rebuild<false><<<tgrid, BLOCK, 0, st>>>(s->K, A, nullptr, nullptr, 0);
+    else
+      k_bin<false><<<tgrid, BLOCK, 0, st>>>(s->K, A, nullptr, nullptr, 0);
   }
-  k_scan<<<s->scan_blocks, BLOCK, 0, st>>>(A);
-  k_scatter<<<tgrid, BLOCK, 0, st>>>(s->K, A);
-  k_sort_gather<<<tgrid, BLOCK, 0, st>>>(s->K, A);
+  if (!fused) {
+    k_scan<<<s->scan_blocks, BLOCK, 0, st>>>(A);
+    k_scatter<<<tgrid, BLOCK, 0, st>>>(s->K, A);
+    k_sort_gather<<<tgrid, BLOCK, 0, st>>>(s->K, A);
+  }
   int e;
   if (ev0 && (e = hip_status(hipEventRecord(ev0, st)))) return e;
   // the Cr-C lists: leading blocks of the staged Cr-Cr list launch, else a launch of their own
@@ -1034,7 +1045,7 @@ MD_API int md_clear_flags(md_system* s, void* stream) {
   k_clear_flags<<<(s->nrep + 63) / 64, 64, 0, st>>>(at<RepState>(s, s->L.state), s->nrep);
   // a build that gave up left its cell counts behind: zero them and lift the abort word
   k_clear_build<<<std::min(4096, (s->ncell_all + BLOCK - 1) / BLOCK + 1), BLOCK, 0, st>>>(
-      at<int>(s, s->L.count), s->ncell_all, at<int>(s, s->L.misc) + 3);
+      at<int>(s, s->L.count), s->ncell_all, at<int>(s, s->L.misc) + 3, at<int>(s, s->L.sync));
   return check_launch();
 }
 

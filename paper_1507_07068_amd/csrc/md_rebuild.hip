@@ -67,6 +67,7 @@ struct BuildArgs {
                          // zero indenter displacement, the carbon's index (as bits) in .w
   long long* scan_state; // [scan_blocks] published chunk sums of k_scan
   int* scan_ticket;      // chunk ticket of k_scan
+  int* sync;             // k_rebuild's counters, zero between builds
   int* hnear;            // [carbon cells]: the cell has a carbon in its 27-cell stencil
   int* idx;
   int* cnt;
@@ -341,41 +342,37 @@ __global__ __launch_bounds__(BLOCK) void k_parts_reduce(const double* __restrict
   }
 }
 
-// Blocks [0, ntiles): one tile of Cr atoms each.  Blocks [ntiles, ...): 256 carbons each.
-// DECIDE (single replica, no forced build): every block takes the skin decision and the
-// cell grid itself from the nparts per-part maxima and boxes (or their partial reductions by
-// k_parts_reduce; so no separate decision launch), all blocks alike; block 0 records them.
-// The indenter reference position, which every block reads for the decision, is recorded by
-// k_scan.
-template <bool DECIDE>
-__global__ __launch_bounds__(BLOCK) void k_bin(Consts K, BuildArgs A, const double* __restrict__ dmax_tile,
-                                               const double* __restrict__ tile_box, int nparts) {
-  BuildGrid g1;
-  if (DECIDE) {
-    g1 = decide_grid(K, A, 0, dmax_tile, tile_box, 0, 0, nparts, threadIdx.x, BLOCK,
+// The skin decision and the cell grid of a single replica without a forced build, taken by every
+// block of a launch alike from the nparts per-part maxima and boxes (or their partial reductions
+// by k_parts_reduce; so no separate decision launch).
+__device__ __forceinline__ BuildGrid decide_alike(const Consts& K, const BuildArgs& A,
+                                                  const double* __restrict__ dmax_tile,
+                                                  const double* __restrict__ tile_box, int nparts) {
+  return decide_grid(K, A, 0, dmax_tile, tile_box, 0, 0, nparts, threadIdx.x, BLOCK,
                      [](double v) { return block_max<BLOCK>(v); });
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      RepState& s0 = A.S[0];
-      record_grid(K, A.R[0], s0, g1);
-      *A.any = g1.need;
-      if (g1.need) {
-        s0.nbuilds += 1;
-        s0.bk0 = 0;
-        *A.nbk = brick_count(s0.bn);
-      }
-    }
-    if (!g1.need) return;
-  } else if (rebuild_off(A)) {
-    return;
+}
+
+// Records that decision (one thread of the launch).  The indenter reference position, which every
+// block reads for the decision, is recorded once no block can read it any more (k_scan, or the
+// end of k_rebuild).
+__device__ __forceinline__ void record_alike(const Consts& K, const BuildArgs& A, const BuildGrid& g1) {
+  RepState& s0 = A.S[0];
+  record_grid(K, A.R[0], s0, g1);
+  *A.any = g1.need;
+  if (g1.need) {
+    s0.nbuilds += 1;
+    s0.bk0 = 0;
+    *A.nbk = brick_count(s0.bn);
   }
-  if (blockIdx.x == 0) {   // fresh state for this build's k_scan
-    for (int t = threadIdx.x; t < A.scan_blocks; t += BLOCK) A.scan_state[t] = 0;
-    if (threadIdx.x == 0) *A.scan_ticket = 0;
-  }
-  for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) {   // (b uniform over the block)
+}
+
+// Work item b of the binning: b < ntiles, a tile of Cr atoms; else 256 carbons.  DECIDE: with the
+// grid just decided (its record may be under way).
+template <bool DECIDE>
+__device__ __forceinline__ void bin_item(const Consts& K, const BuildArgs& A, const BuildGrid& g1, int b) {
   if (b < A.ntiles) {
     const int r = A.tile_rep[b];
-    if (!DECIDE && !A.S[r].rebuild) continue;
+    if (!DECIDE && !A.S[r].rebuild) return;
     const RepDesc& d = A.R[r];
     const int64_t i = (int64_t)b * TILE + threadIdx.x;
     const bool live = i < (int64_t)d.a0 + d.n;
@@ -425,7 +422,26 @@ __global__ __launch_bounds__(BLOCK) void k_bin(Consts K, BuildArgs A, const doub
       A.hrank[k] = atomicAdd(&A.count[hid], 1);
     }
   }
+}
+
+// Blocks stride over the binning's work items.  DECIDE: every block takes the decision first;
+// block 0 records it.
+template <bool DECIDE>
+__global__ __launch_bounds__(BLOCK) void k_bin(Consts K, BuildArgs A, const double* __restrict__ dmax_tile,
+                                               const double* __restrict__ tile_box, int nparts) {
+  BuildGrid g1;
+  if (DECIDE) {
+    g1 = decide_alike(K, A, dmax_tile, tile_box, nparts);
+    if (blockIdx.x == 0 && threadIdx.x == 0) record_alike(K, A, g1);
+    if (!g1.need) return;
+  } else if (rebuild_off(A)) {
+    return;
   }
+  if (blockIdx.x == 0) {   // fresh state for this build's k_scan
+    for (int t = threadIdx.x; t < A.scan_blocks; t += BLOCK) A.scan_state[t] = 0;
+    if (threadIdx.x == 0) *A.scan_ticket = 0;
+  }
+  for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) bin_item<DECIDE>(K, A, g1, b);   // (b uniform over the block)
 }
 
 // Exclusive scan of all cell counts in one launch: each block scans SCAN_CHUNK cells and
@@ -436,16 +452,9 @@ __global__ __launch_bounds__(BLOCK) void k_bin(Consts K, BuildArgs A, const doub
 constexpr int SCAN_PER_THREAD = 8;
 constexpr long long SCAN_AGG = 1ll << 32, SCAN_INCL = 2ll << 32;
 
-__global__ __launch_bounds__(BLOCK) void k_scan(BuildArgs A) {
-  if (rebuild_off(A)) return;
-  __shared__ int chunk_sh, excl_sh;
-  if (threadIdx.x == 0) chunk_sh = atomicAdd(A.scan_ticket, 1);
-  __syncthreads();
-  const int b = chunk_sh;
-  if (A.commit_ref && b == 0 && threadIdx.x == 0) {   // k_bin decided: this build's indenter position
-    RepState& s0 = A.S[0];
-    s0.ind_z_ref = s0.ind_z;
-  }
+// Chunk b (blocks take them in ascending order).
+__device__ __forceinline__ void scan_chunk(const BuildArgs& A, int b) {
+  __shared__ int excl_sh;
   const int c0 = b * A.scan_chunk + threadIdx.x * SCAN_PER_THREAD;
   int v[SCAN_PER_THREAD];
   int sum = 0;
@@ -520,19 +529,31 @@ __global__ __launch_bounds__(BLOCK) void k_scan(BuildArgs A) {
   }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_scatter(Consts K, BuildArgs A) {
+__global__ __launch_bounds__(BLOCK) void k_scan(BuildArgs A) {
   if (rebuild_off(A)) return;
-  for (int r = blockIdx.x; K.nrep > 1 && r < K.nrep; r += gridDim.x) {   // the bricks' replicas
+  __shared__ int chunk_sh;
+  if (threadIdx.x == 0) chunk_sh = atomicAdd(A.scan_ticket, 1);
+  __syncthreads();
+  const int b = chunk_sh;
+  if (A.commit_ref && b == 0 && threadIdx.x == 0) {   // k_bin decided: this build's indenter position
+    RepState& s0 = A.S[0];
+    s0.ind_z_ref = s0.ind_z;
+  }
+  scan_chunk(A, b);
+}
+
+// Work item b of the scatter into cell order, as bin_item.
+__device__ __forceinline__ void scatter_item(const Consts& K, const BuildArgs& A, int b) {
+  for (int r = b; K.nrep > 1 && r < K.nrep; r += A.nbin) {   // the bricks' replicas
     const int b0 = A.S[r].bk0, nb = brick_count(A.S[r].bn);
     for (int t = threadIdx.x; t < nb; t += BLOCK) A.bk_rep[b0 + t] = r;
   }
-  for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) {   // (b uniform over the block)
   if (b < A.ntiles) {
     const int r = A.tile_rep[b];
-    if (!A.S[r].rebuild) continue;
+    if (!A.S[r].rebuild) return;
     const RepDesc& d = A.R[r];
     const int64_t i = (int64_t)b * TILE + threadIdx.x;
-    if (i >= (int64_t)d.a0 + d.n) continue;
+    if (i >= (int64_t)d.a0 + d.n) return;
     const int cid = A.cellid[i];
     const int pos = d.a0 + (A.start[cid] - A.start[d.g0]) + A.crank[i];
     A.perm[pos] = (int)i;
@@ -550,9 +571,9 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(Consts K, BuildArgs A) {
     }
   } else {
     const int64_t k = (int64_t)(b - A.ntiles) * BLOCK + threadIdx.x;
-    if (k >= A.ctot) continue;
+    if (k >= A.ctot) return;
     const int r = A.c_rep[k];
-    if (!A.S[r].rebuild) continue;
+    if (!A.S[r].rebuild) return;
     const RepDesc& d = A.R[r];
     const int hid = A.hcell[k];
     const int rank = A.hrank[k];
@@ -579,20 +600,22 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(Consts K, BuildArgs A) {
       }
     }
   }
-  }
 }
 
-// One lane per slot in cell order.  Blocks [0, ntiles): Cr slots, one tile each; blocks
-// [ntiles, ...): 256 carbon slots each.  A slot's final position is the start of its cell
+__global__ __launch_bounds__(BLOCK) void k_scatter(Consts K, BuildArgs A) {
+  if (rebuild_off(A)) return;
+  for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) scatter_item(K, A, b);   // (b uniform over the block)
+}
+
+// One lane per slot in cell order.  Work item b < ntiles: a tile of Cr slots; else 256 carbon
+// slots.  A slot's final position is the start of its cell
 // plus the number of atoms of that cell with a smaller (cell, id) key (cells hold a few
 // atoms), so the final order is canonical; the atom's state is gathered there.
-__global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
-  if (rebuild_off(A)) return;
-  for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) {   // (b uniform over the block)
+__device__ __forceinline__ void sort_item(const Consts& K, const BuildArgs& A, int b) {
   if (b < A.ntiles) {
     const int r = A.tile_rep[b];
     RepState& S = A.S[r];
-    if (!S.rebuild) continue;
+    if (!S.rebuild) return;
     const RepDesc& d = A.R[r];
     const int u = b * TILE + threadIdx.x;
     bool near = false;
@@ -651,9 +674,9 @@ __global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
     }
   } else {
     const int64_t u = (int64_t)(b - A.ntiles) * BLOCK + threadIdx.x;
-    if (u >= A.ctot) continue;
+    if (u >= A.ctot) return;
     const int r = A.c_rep[u];   // carbon slots of a replica are its carbon index range
-    if (!A.S[r].rebuild) continue;
+    if (!A.S[r].rebuild) return;
     const RepDesc& d = A.R[r];
     const int e = A.hlist[u];
     const int c = A.hcell[e];
@@ -671,6 +694,107 @@ __global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
                                         __longlong_as_double((long long)e));
     if (u == s0) A.count[c] = 0;   // zero again for the next rebuild
   }
+}
+
+__global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
+  if (rebuild_off(A)) return;
+  for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) sort_item(K, A, b);   // (b uniform over the block)
+}
+
+// k_bin, k_scan, k_scatter and k_sort_gather in one launch, for systems of few work items
+// (at most REBUILD_ITEMS).  A step without a rebuild, most of a run's, then pays for one launch
+// that finds nothing to do in place of four (about 2 us each, beside passes of 8 to 20 us).
+// Blocks take the binning's items from a counter and keep them for the later phases, each of
+// which waits for the end of the one before: only blocks that hold items keep another back, and
+// those run, so the waits end whichever of the launch's blocks have been placed (they are bounded
+// all the same).  The fences around a wait carry the phase's stores to every XCD.
+enum { SY_TAKEN = 0, SY_BIN, SY_SCAN, SY_SCATTER, SY_LEFT, SY_WORDS };
+constexpr int SYNC_STRIDE = 16;                      // a counter to a 64-byte line
+constexpr int SYNC_INTS = SY_WORDS * SYNC_STRIDE;
+constexpr int PHASE_SPINS = 1 << 22;
+// A build's phases in one launch take 21 us at 8 items, as the four launches do, but 36 at 41
+// and 46 at 64, where the waits cost more than launches.  Films of 100 steps, this against the
+// four launches: 1,024 atoms 0.89 of the time (cold) and 0.94 (melting, a rebuild every few
+// steps), 8,192 atoms 0.90 and 0.97, 16,000 0.96 and 1.06.
+constexpr int REBUILD_ITEMS = 48;
+
+// Counts the block's `mine` items of a phase of `items` and waits for the others' (false: given
+// up, as a scan that does; scan: or one of its chunks did).
+__device__ __forceinline__ bool phase_end(const BuildArgs& A, int* done, int mine, int items, bool scan = false) {
+  __shared__ int ok_sh;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // each thread's stores of this phase
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (mine) atomicAdd(done, mine);
+    int spins = 0;
+    bool ok = true;
+    while (ok && __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < items) {
+      if (++spins > PHASE_SPINS) {
+        A.S[0].sync_timeout = 1;
+        *A.any = 0;
+        __hip_atomic_store(A.abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ok = false;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if (ok && scan) ok = __hip_atomic_load(A.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    ok_sh = ok ? 1 : 0;
+  }
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the other blocks' stores
+  const bool ok = ok_sh != 0;
+  __syncthreads();   // (ok_sh is free again)
+  return ok;
+}
+
+template <bool DECIDE>
+__global__ __launch_bounds__(BLOCK) void k_rebuild(Consts K, BuildArgs A, const double* __restrict__ dmax_tile,
+                                                   const double* __restrict__ tile_box, int nparts) {
+  BuildGrid g1;
+  if (DECIDE) {
+    g1 = decide_alike(K, A, dmax_tile, tile_box, nparts);
+    if (!g1.need) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) record_alike(K, A, g1);
+      return;
+    }
+  } else if (rebuild_off(A)) {
+    return;
+  }
+  __shared__ int own[REBUILD_ITEMS + 1];   // this block's items, ascending
+  int n = 0;
+  while (true) {
+    if (threadIdx.x == 0) own[n] = atomicAdd(A.sync + SY_TAKEN * SYNC_STRIDE, 1);
+    __syncthreads();
+    const int b = own[n];
+    if (b >= A.nbin) break;
+    ++n;
+    if (b == 0) {   // (the record and the scan's fresh state are part of the phase)
+      if (DECIDE && threadIdx.x == 0) record_alike(K, A, g1);
+      for (int t = threadIdx.x; t < A.scan_blocks; t += BLOCK) A.scan_state[t] = 0;
+    }
+    bin_item<DECIDE>(K, A, g1, b);
+  }
+  if (!phase_end(A, A.sync + SY_BIN * SYNC_STRIDE, n, A.nbin)) return;
+  // the scan's chunks go to the holders of the items of the same number (modulo their count); a
+  // holder takes its chunks in ascending order, so the lowest unfinished one is always under way
+  int chunks = 0;
+  for (int c0 = 0; c0 < A.scan_blocks; c0 += A.nbin)
+    for (int k = 0; k < n; ++k)
+      if (c0 + own[k] < A.scan_blocks) {
+        scan_chunk(A, c0 + own[k]);
+        __syncthreads();   // (the chunk's shared words are free again)
+        ++chunks;
+      }
+  // (a scan that gave up: nothing is scattered, and the counters stay until md_clear_flags)
+  if (!phase_end(A, A.sync + SY_SCAN * SYNC_STRIDE, chunks, A.scan_blocks, true)) return;
+  for (int k = 0; k < n; ++k) scatter_item(K, A, own[k]);
+  if (!phase_end(A, A.sync + SY_SCATTER * SYNC_STRIDE, n, A.nbin)) return;
+  for (int k = 0; k < n; ++k) sort_item(K, A, own[k]);
+  // the last block to leave, when every block has decided and looked for its last item, records
+  // the indenter position and clears the counters for the next build
+  if (threadIdx.x == 0 && atomicAdd(A.sync + SY_LEFT * SYNC_STRIDE, 1) == (int)gridDim.x - 1) {
+    if (A.commit_ref) A.S[0].ind_z_ref = A.S[0].ind_z;
+    for (int t = 0; t < SYNC_INTS; t += SYNC_STRIDE) A.sync[t] = 0;
   }
 }
 
