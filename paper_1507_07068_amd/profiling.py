@@ -51,7 +51,7 @@ def steps(d: str) -> str:
     groups, cur, prev = [], None, ""
     for n, s, e in rows:
         k = short_name(n)
-        first_build = k.startswith("k_decide") or (k.startswith("k_bin") and not prev.startswith("k_decide"))
+        first_build = k.startswith("k_decide") or (k.startswith(("k_bin", "k_rebuild")) and not prev.startswith("k_decide"))
         if k.startswith("k_kick_drift") or (first_build and not prev.startswith("k_kick_drift")):
             cur = []
             groups.append(cur)

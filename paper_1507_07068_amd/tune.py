@@ -3,11 +3,12 @@
 Two shape parameters change speed but not results:
 
 * ``tpa``: the lanes that share one atom in the density and force passes (1, 2, 4 or 8; the
-  list is interleaved to match).  Few lanes per atom leave long serial gathers; many lanes
+  list is interleaved to match; the paper's form, whose lists are long, takes 4 or 8 whatever
+  the interleave).  Few lanes per atom leave long serial gathers; many lanes
   spend more on the cross-lane reduction and on idle lanes of short lists.
-* ``list_tgt``: the atoms a work item of the list build aims at.  Smaller items spread a
-  rebuild over more blocks (good for many small replicas); larger ones stage each cell row for
-  more centres.
+* ``list_tgt``: below 224 the list build gives each brick of cells to 224 / ``list_tgt`` blocks,
+  which spreads a rebuild over more of them (good for many small replicas); from 224 on one
+  block stages a brick for all its centres.
 
 The best choice depends on the list lengths, on the atoms a launch has to fill the chip with,
 and on how often lists are rebuilt, so it is measured.  Each candidate runs a short stretch of
