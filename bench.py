@@ -43,7 +43,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_c4_film_8m.txt")
 SOURCES = {k: [os.path.join(ROOT, "paper_1507_07068_amd", "csrc", f) for f in v]
            for k, v in (("force", ("md_forces.hip", "md_device.hpp")),
                         ("density", ("md_forces.hip", "md_device.hpp")),
-                        ("list", ("md_rebuild.hip", "md_device.hpp")))}
+                        ("list", ("md_rebuild.hip", "md_bricks.hpp", "md_device.hpp")))}
 
 WORKLOADS = {
     "c0": (0, "bcc_bulk_10x10x10_2k_periodic"),
