@@ -26,7 +26,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 struct Layout {
   size_t desc, state, tile_rep, c_rep, misc, sync, bk_rep, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
       tf, tfixed, tid, count, start, hcell, hrank, hlist, hsorted, scan_state, hnear, near, fme, p_embed, p_force,
-      p_morse, p_kin, dm, dmax_p, tbox_p, base, midx, mcnt, mref, total;
+      p_morse, p_kin, dm, dmax_p, tbox_p, base, midx, mcnt, mref, msum, total;
 };
 
 constexpr int MISC_INTS = 16;    // rebuild flag, status words
@@ -165,6 +165,7 @@ Layout make_layout(const md_system& s) {
   L.midx = take(s.p.icap ? sizeof(int) * n * (size_t)s.mid_cap : 0);
   L.mcnt = take(s.p.icap ? sizeof(int) * n : 0);
   L.mref = take(s.p.icap ? sizeof(float) * 4 * n : 0);
+  L.msum = take(s.p.icap ? sizeof(unsigned long long) * n : 0);
   L.total = s.p.icap ? o : L.base;
   return L;
 }
@@ -771,17 +772,21 @@ MD_API int md_build_neighbors(md_system* s, const md_atoms* a, const md_lists* l
 
 namespace {
 
-// Two-tier lists: the inner list refilled from the outer one at the current positions.
-int inner_list(md_system* s, const md_atoms* a, const md_lists* l, hipStream_t st) {
+// Two-tier lists: the inner list refilled from the outer one at the current positions (first: the
+// first refill of a call of the caller's, who may have changed the outer lists since the last one).
+int inner_list(md_system* s, const md_atoms* a, const md_lists* l, hipStream_t st, bool first) {
   if (!s->p.icap) return MD_OK;
   const RepDesc* R = at<RepDesc>(s, s->L.desc);
   RepState* S = at<RepState>(s, s->L.state);
   const int* tr = at<int>(s, s->L.tile_rep);
   const double4* q = qcur(s, a);
   float4* qf = at<float4>(s, s->L.tqf);
-  const MidList M{s->mid ? at<int>(s, s->L.midx) : nullptr, at<int>(s, s->L.mcnt), at<float4>(s, s->L.mref), s->mid_cap};
+  const MidList M{s->mid ? at<int>(s, s->L.midx) : nullptr, at<int>(s, s->L.mcnt), at<float4>(s, s->L.mref),
+                  at<unsigned long long>(s, s->L.msum), s->mid_cap};
   const int nm = grid_tiles(s) * MID_G;
   k_inner_pos<<<grid_tiles(s), BLOCK, 0, st>>>(s->K, R, S, tr, q, qf, M);
+  if (s->mid && first)
+    k_mid_check<<<grid_tiles(s) * (TILE / WAVE), CHECK_WAVES * WAVE, 0, st>>>(s->K, R, S, tr, l->idx, l->cnt, M);
   if (s->mid) k_mid_list<<<std::min(nm, 4 * s->tile_grid), BLOCK, 0, st>>>(s->K, R, S, tr, q, qf, l->idx, l->cnt, M, nm);
   k_inner_list<<<grid_tiles(s) * INNER_G, BLOCK, 0, st>>>(s->K, R, S, tr, q, qf, l->idx, l->cnt, M, l->iidx, l->icnt);
   return check_launch();
@@ -793,7 +798,7 @@ int eam_density(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
                 hipStream_t st, bool inner = true) {
   const bool mixed = flags & MD_F_MIXED, energy = flags & MD_F_ENERGY;
   if (inner) {
-    const int e = inner_list(s, a, l, st);
+    const int e = inner_list(s, a, l, st, true);
     if (e) return e;
   }
   switch (s->K.ln) {
@@ -944,7 +949,7 @@ MD_API int md_run(md_system* s, const md_atoms* a, const md_lists* l, int32_t ns
     const bool morse = s->ctot > 0;
     const uint32_t ef = mixed | (en ? MD_F_ENERGY : 0);
     if (ev[6] && (e = hip_status(hipEventRecord(ev[6], st)))) return e;
-    if ((e = inner_list(s, a, l, st))) return e;
+    if ((e = inner_list(s, a, l, st, k == 1))) return e;
     if (ev[7] && (e = hip_status(hipEventRecord(ev[7], st)))) return e;
     if (ev[4] && (e = hip_status(hipEventRecord(ev[4], st)))) return e;
     if ((e = eam_density(s, a, l, MD_F_DENSITY | ef, nullptr, morse, st, false))) return e;

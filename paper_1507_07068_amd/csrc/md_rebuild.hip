@@ -1339,7 +1339,7 @@ __global__ __launch_bounds__(BLOCK) void k_xlist(Consts K, BuildArgs A) {
 //
 // The source is a middle list: the outer entries closer than r* + mid_skin at the positions mref,
 // taken again (k_mid_list) when an atom of the replica has moved more than mid_skin / 2 from
-// there, or the outer list is new.  Every pair within r* is then in it, as every pair within r*
+// there, the outer list is new, or a call finds other entries in it (k_mid_check).  Every pair within r* is then in it, as every pair within r*
 // is in the outer list, so the inner list is the one that the outer list itself gives.  What
 // bounds the refill is the gather of one position per source entry: the paper's form has about
 // 940 outer entries an atom and 260 middle ones.  On the 216k-atom film the refill from the outer
@@ -1353,8 +1353,63 @@ struct MidList {
   int* idx;       // [cap][ntot], laid out as the outer list
   int* cnt;       // [ntot]; < 0: more entries than cap, and the outer list is this atom's source
   float4* ref;    // [ntot] the positions (as k_inner_pos gives them) it was taken at
+  unsigned long long* sum;   // [ntot] entry_hash summed over the outer entries it was taken from
   int cap;
 };
+
+// Hash of entry k of an atom's outer list (odd multipliers: the fractions of the roots of 2 and 3).
+// The entries' hashes are added up, in any order, to a 64-bit fingerprint of the list.
+__device__ __forceinline__ unsigned long long entry_hash(int k, int e) {
+  unsigned long long z = ((unsigned long long)(unsigned)k << 32 | (unsigned)e) * 0x6A09E667F3BCC909ull;
+  z = (z ^ (z >> 32)) * 0xBB67AE8584CAA73Bull;
+  return z ^ (z >> 32);
+}
+
+// Middle lists are kept from one call to the next, while the outer lists lie in the caller's arrays
+// (and may be other arrays in the next call): a replica whose outer lists are not, entry for entry,
+// those its middle lists were taken from has them marked.  The first refill of a call runs it; inside
+// md_run only its own builds write the lists.  A lane per atom and CHECK_WAVES wavefronts over its
+// entries, read once and coalesced.
+constexpr int CHECK_WAVES = 16;
+__global__ __launch_bounds__(CHECK_WAVES* WAVE) void k_mid_check(Consts K, const RepDesc* __restrict__ R,
+                                                                RepState* __restrict__ S,
+                                                                const int* __restrict__ tile_rep,
+                                                                const int* __restrict__ idx, const int* __restrict__ cnt,
+                                                                MidList M) {
+  constexpr int PER_TILE = TILE / WAVE;   // blocks per tile
+  constexpr int U = 4;                    // entries in flight per lane
+  const int r = tile_rep[blockIdx.x / PER_TILE];
+  const RepDesc& d = R[r];
+  __shared__ int ok_sh;
+  if (threadIdx.x == 0) ok_sh = S[r].mid_ok;   // (another block may clear it meanwhile)
+  __syncthreads();
+  if (!ok_sh) return;
+  const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+  const int64_t i = (int64_t)blockIdx.x * WAVE + lane;
+  const bool live = i < (int64_t)d.a0 + d.n;
+  const int n = live ? cnt[i] : 0;
+  const int T = K.lt;
+  const unsigned stride = (unsigned)K.ntot * T, base = (unsigned)(live ? i : 0) * T;
+  unsigned long long h = 0;
+  for (int k0 = w * U; k0 < n; k0 += CHECK_WAVES * U) {
+    int e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(k0 + u, n - 1);
+      e[u] = idx[((unsigned)k >> K.lt_shift) * stride + base + (unsigned)(k & (T - 1))];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) h += k0 + u < n ? entry_hash(k0 + u, e[u]) : 0ull;
+  }
+  __shared__ unsigned long long part[CHECK_WAVES][WAVE];
+  part[w][lane] = h;
+  __syncthreads();
+  if (w == 0 && live) {
+    unsigned long long sum = 0;
+    for (int t = 0; t < CHECK_WAVES; ++t) sum += part[t][lane];
+    if (sum != M.sum[i]) S[r].mid_ok = 0;
+  }
+}
 
 // Bound on the error of an FP32 position relative to the grid origin, per axis, for atoms within
 // R of the grid, images included (the list build's).
@@ -1456,6 +1511,7 @@ __device__ __forceinline__ void filter_list(const Consts& K, const RepDesc& d, R
   const int gshift = (int)(threadIdx.x % WAVE) - sub;   // the group's first lane
   const unsigned below = (1u << sub) - 1u;
   int c = 0;        // entries kept so far
+  unsigned long long h = 0;   // MID: the fingerprint of this lane's entries
   int e = sub < n ? src[at_k(sub)] : 0;   // (slot 0 stands in for an entry past the list)
   for (int m0 = 0; m0 < nw; m0 += G) {
     const int k = m0 + sub;
@@ -1485,6 +1541,7 @@ __device__ __forceinline__ void filter_list(const Consts& K, const RepDesc& d, R
       }
     }
     keep = keep && k < n;
+    if (MID && k < n) h += entry_hash(k, e);
     const unsigned gm = (unsigned)(__ballot(keep) >> gshift) & ((1u << G) - 1u);
     if (keep) {
       const int j = c + __popc(gm & below);
@@ -1493,10 +1550,15 @@ __device__ __forceinline__ void filter_list(const Consts& K, const RepDesc& d, R
     c += __popc(gm);
     e = en;
   }
+  if (MID) {
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) h += __shfl_xor(h, o, WAVE);
+  }
   if (live && sub == 0) {
     if (MID) {
       ocnt[i] = c > ocap ? -1 : c;
       M.ref[i] = pif;
+      M.sum[i] = h;
     } else {
       ocnt[i] = min(c, ocap);
       if (c > ocap) atomicMax(&s.ioverflow, c);
