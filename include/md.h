@@ -225,7 +225,9 @@ MD_API int64_t md_replica_offset(const md_system *sys, int32_t r);
 MD_API size_t md_workspace_bytes(const md_system *sys);
 
 /* Bind a caller-owned device workspace of at least md_workspace_bytes bytes: writes the
- * replica descriptors, clears flags, and synchronises `stream`.  MD_ERR_ARG if too small. */
+ * replica descriptors, clears flags, and synchronises `stream`.  MD_ERR_ARG if too small.
+ * With two-tier lists the size that the same system needs with icap 0 is enough: without the
+ * middle lists, the inner lists are refilled from the outer ones, with the same results. */
 MD_API int md_workspace_bind(md_system *sys, void *ws, size_t bytes, void *stream);
 
 /* Bytes of the library's static device scratch (one per GPU): see md_workspace_bind_static. */

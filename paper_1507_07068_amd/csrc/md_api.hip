@@ -608,7 +608,7 @@ int bind_workspace(md_system* s, void* ws, size_t bytes, hipStream_t st) {
 }  // namespace
 
 MD_API int md_workspace_bind(md_system* s, void* ws, size_t bytes, void* stream) {
-  if (!s || !ws || bytes < s->L.total) return MD_ERR_ARG;
+  if (!s || !ws || bytes < s->L.base) return MD_ERR_ARG;   // (without room for the middle lists: see MidList)
   if (((uintptr_t)ws) % ALIGN) return MD_ERR_ARG;
   if (s->static_dev >= 0) {   // give up a static scratch this system held
     const md_system* me = s;

@@ -103,3 +103,35 @@ def test_batch_of_a_fast_and_a_slow_replica(how, precision):
     moved = [np.abs(min_image_diff(both[-1][r]["x"], s.x, s)).max() for r, s in enumerate(reps)]
     half = 0.5 * 0.08 * reps[0].cutoff   # of the middle lists' own skin
     assert moved[0] < half < 1.2 * half < moved[1], moved
+
+
+def test_workspace_without_the_middle_lists():
+    """The size that the system needs with icap 0 is taken (and gives the same forces), a smaller
+    one is refused."""
+    import ctypes as C
+
+    import torch
+    s = I.two_tier(I.bulk(16, seed=74, noise=0.03, temperature=300.0))
+    lib = md.load_library()
+    p = md.make_params(s, cap=1152, xcap=160, tpa=2)
+    h = C.c_void_p()
+    desc = (md.ReplicaDesc * 1)(md.make_replica_desc(s))
+    assert lib.md_system_create(C.cast(desc, C.c_void_p), 1, C.byref(p), C.byref(h)) == md.MD_OK
+    need = int(lib.md_workspace_bytes(h))
+    lib.md_system_destroy(h)
+    sims = [md.Simulation(s, cap=1152, xcap=160, tpa=2, icap=256) for _ in range(2)]
+    small = sims[1]
+    whole = int(lib.md_workspace_bytes(small.handle))
+    print(f"[case] workspace {need} of {whole} bytes", flush=True)
+    assert need + 4 * 256 * s.n < whole
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    assert ws.data_ptr() % 256 == 0
+    assert lib.md_workspace_bind(small.handle, C.c_void_p(ws.data_ptr()), need - 1, small.stream) == md.MD_ERR_ARG
+    small.ws = ws
+    assert lib.md_workspace_bind(small.handle, C.c_void_p(ws.data_ptr()), need, small.stream) == md.MD_OK
+    for m in sims:
+        m.initial_forces()
+        m.md_run(20)
+    a, b = (m.state()[0] for m in sims)
+    for k in ("x", "v", "f", "dF"):
+        assert np.array_equal(a[k], b[k]), k
