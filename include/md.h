@@ -220,8 +220,8 @@ MD_API int64_t md_system_carbons(const md_system *sys);
 MD_API int64_t md_replica_offset(const md_system *sys, int32_t r);
 
 /* Bytes of device workspace the system needs (cell grids, sort buffers, reference
- * positions, flags, reduction partials; with two-tier lists the middle lists, which speed up
- * the inner lists' refill). */
+ * positions, flags, reduction partials; with two-tier lists whose outer list is much the longer
+ * one the middle lists, which speed up the inner lists' refill). */
 MD_API size_t md_workspace_bytes(const md_system *sys);
 
 /* Bind a caller-owned device workspace of at least md_workspace_bytes bytes: writes the

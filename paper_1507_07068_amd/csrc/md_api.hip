@@ -39,6 +39,14 @@ constexpr int64_t LANES8_ATOMS = 49152;
 // form.  They are taken again, at four times a refill, when an atom has moved half of that; 0.12
 // made each refill 7 % dearer, 0.05 no cheaper (the same lattice shells).
 constexpr double MID_SKIN = 0.08;
+// They are kept where the outer lists are long, and longer by this much than they are (by the volumes):
+// a refill from the outer list costs a gather per outer entry, one from the middle list a gather per
+// middle entry and now and then (at each second step past melting) a pass over the outer list that
+// costs more.  216k-atom film, with against without: the paper's form (middle lists of 258), 20 cold
+// steps: volumes 1.00 1.03 of the time, 1.31 0.92, 2.01 0.72, 3.9 0.47 (300 K; 2500 K: 1.04, 0.95, 0.74).
+// The synthetic form, with 26 to 64 outer entries, never: 1.00 to 1.13 cold, 1.16 to 1.22 past melting.
+constexpr double MID_VOLUMES = 1.25;
+constexpr double MID_ENTRIES = 150.0;
 constexpr int SCAN_CHUNK = 2048; // cells per block of the cell-count scan
 constexpr int64_t DECIDE_IN_BIN_MAX_LOADS = (int64_t)1 << 22;   // part loads over all k_bin blocks
 constexpr int PARTS_REDUCED = 64;   // partial reductions of a large single replica's parts
@@ -62,7 +70,7 @@ struct md_system {
   Layout L;
   char* ws;
   int scan_blocks;
-  int mid_cap = 0;        // two-tier lists: capacity of the middle lists
+  int mid_cap = 0;        // two-tier lists: capacity of the middle lists (0: none are kept)
   bool mid = false;       // the bound workspace holds them
   bool list_mix;   // some periodic axis has fewer than 3 list cells
   bool have_embed, have_force;
@@ -105,6 +113,14 @@ namespace {
 int cells_along(double len, double edge) {
   double n = std::floor(len / (edge * (1.0 + 1e-9)));
   return n < 1.0 ? 1 : (int)n;
+}
+
+// About how many entries a list of radius r holds in the solid: the paper's form names its neighbour
+// distance re (close packing at it: 178 for its 8.56 A, where the benchmark's lattice has 206); the
+// synthetic form's cutoff takes in two neighbour shells.
+double entries_within(const md_params& p, double r) {
+  if (p.potential == MD_POT_PAPER) return 5.92 * std::pow(r / p.paper.re, 3);
+  return 20.0 * std::pow(r / p.eam.c, 3);
 }
 
 Layout make_layout(const md_system& s) {
@@ -162,11 +178,11 @@ Layout make_layout(const md_system& s) {
   L.p_kin = take(sizeof(double) * nt * s.K.ln);
   L.base = o;
   // the middle lists of two-tier lists (a workspace without them serves too: see MidList)
-  L.midx = take(s.p.icap ? sizeof(int) * n * (size_t)s.mid_cap : 0);
-  L.mcnt = take(s.p.icap ? sizeof(int) * n : 0);
-  L.mref = take(s.p.icap ? sizeof(float) * 4 * n : 0);
-  L.msum = take(s.p.icap ? sizeof(unsigned long long) * n : 0);
-  L.total = s.p.icap ? o : L.base;
+  L.midx = take(s.mid_cap ? sizeof(int) * n * (size_t)s.mid_cap : 0);
+  L.mcnt = take(s.mid_cap ? sizeof(int) * n : 0);
+  L.mref = take(s.mid_cap ? sizeof(float) * 4 * n : 0);
+  L.msum = take(s.mid_cap ? sizeof(unsigned long long) * n : 0);
+  L.total = s.mid_cap ? o : L.base;
   return L;
 }
 
@@ -516,7 +532,9 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   K.icap = p->icap;
   K.mid_skin = MID_SKIN * cut;
   K.mid_rc_sq = (cut + K.mid_skin) * (cut + K.mid_skin);
-  if (p->icap) {   // the inner capacity times the volume, a whole number of interleaved groups
+  if (p->icap && std::pow(rlist / (cut + K.mid_skin), 3) >= MID_VOLUMES &&
+      std::min((double)p->cap, entries_within(*p, rlist)) >= MID_ENTRIES) {
+    // the inner capacity times the volume, a whole number of interleaved groups
     const double g = (1.0 + MID_SKIN) * (1.0 + MID_SKIN) * (1.0 + MID_SKIN);
     s->mid_cap = std::min(p->cap, (int)((std::ceil(p->icap * g) + 7.0) / 8.0) * 8);
   }
@@ -576,7 +594,7 @@ namespace {
 // Takes ws as the workspace of s: cleared, descriptors written, stream synchronised.
 int bind_workspace(md_system* s, void* ws, size_t bytes, hipStream_t st) {
   s->ws = (char*)ws;
-  s->mid = s->p.icap && bytes >= s->L.total;
+  s->mid = s->mid_cap && bytes >= s->L.total;
   int e;
   if ((e = hip_status(hipMemsetAsync(ws, 0, s->L.base, st)))) return e;
   if ((e = hip_status(hipMemcpyAsync(at<RepDesc>(s, s->L.desc), s->desc.data(),
