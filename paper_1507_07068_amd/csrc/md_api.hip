@@ -24,7 +24,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Byte offsets of the workspace regions.
 struct Layout {
-  size_t desc, state, tile_rep, c_rep, misc, sync, bk_rep, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
+  size_t desc, state, tile_rep, c_rep, misc, sync, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
       tf, tfixed, tid, count, start, hcell, hrank, hlist, hsorted, scan_state, hnear, near, fme, p_embed, p_force,
       p_morse, p_kin, dm, dmax_p, tbox_p, base, midx, mcnt, mref, msum, total;
 };
@@ -135,7 +135,6 @@ Layout make_layout(const md_system& s) {
   L.desc = take(sizeof(RepDesc) * s.nrep);
   L.state = take(sizeof(RepState) * s.nrep);
   L.tile_rep = take(sizeof(int) * nt);
-  L.bk_rep = take(s.nrep > 1 ? sizeof(int) * (size_t)s.bcap : 0);
   L.c_rep = take(sizeof(int) * (size_t)s.ctot);
   L.misc = take(sizeof(int) * MISC_INTS);
   L.sync = take(sizeof(int) * SYNC_INTS);
@@ -236,14 +235,14 @@ int scan_spin_limit() {
 int list_parts(const md_system* s) {
   return (int)std::max<int64_t>(s->list_parts, std::min<int64_t>(8, s->cus / std::max<int64_t>(1, s->best)));
 }
-// Blocks of the list build: about as many as there are brick shares (their number is known on
+// Blocks of the list build: about as many as there are shares of work items (their number is known on
 // the device; the blocks stride over them), up to LIST_WAVES times what the chip holds (three of
 // its blocks per compute unit).  A step without a rebuild pays for dispatching them all: 12.9 us
 // (now 7.3) for the 26,000 shares of an 8M-atom film.  Ten steps of it, list launches in all: 7.98 ms with a
 // block per share, 7.65 at 16 times the chip, 7.84 at 8, 8.28 at 4, 9.30 at 2 (uneven shares).
 constexpr int LIST_WAVES = 16;
 int list_blocks(const md_system* s) {
-  return (int)std::min<int64_t>(std::min<int64_t>(s->bcap, s->best + s->best / 4 + 8) * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
+  return (int)std::min<int64_t>((std::max<int64_t>(s->best + s->best / 4, s->ntot / 400) + 8) * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
 }
 
 // Grid of the kernels that walk the near-indenter atoms (one wavefront per atom, grid-stride).
@@ -677,8 +676,10 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   A.R = at<RepDesc>(s, s->L.desc);
   A.S = at<RepState>(s, s->L.state);
   A.tile_rep = at<int>(s, s->L.tile_rep);
-  A.bk_rep = at<int>(s, s->L.bk_rep);
-  A.nbk = misc + 2;
+  // (the shadow buffer that the next drift writes is free until then, and holds an item per atom)
+  A.items = s->list_mix ? nullptr : qsnext(s);
+  A.nitems = misc + 2;
+  A.nbk = misc + 4;
   A.parts = list_parts(s);
   A.c_rep = at<int>(s, s->L.c_rep);
   A.any = misc + 0;

@@ -54,7 +54,7 @@ struct alignas(64) RepState {
   double gedge[3];        // cell edge of that grid (1 / ginv)
   double qscale;          // fixed-point scale of the shadow positions (a power of two)
   int gd[3];
-  int bn[3];              // bricks along each axis (see BrickGrid)
+  int bn[3];              // bricks along each axis (see choose_bricks)
   int bk0;                // its first brick in the launch-wide numbering
   float scr_lo, scr_hi;   // band of the list build's FP32 screen
 };

@@ -33,8 +33,11 @@ struct BuildArgs {
   const RepDesc* R;
   RepState* S;
   const int* tile_rep;   // [ntiles]
-  int* bk_rep;           // [bricks at capacity] replica of each brick (several replicas only)
-  int* nbk;              // bricks of all replicas
+  int4* items;           // [ntot] the list build's work items: replica, brick of it, first and last + 1
+                         // of the brick's centers (null: k_list_rows builds the lists)
+  int* nitems;           // their number
+  int* nbk;              // bricks of all replicas, each the work item of its number (0: more than
+                         // there is room for, and empty ones have no item)
   const int* c_rep;      // [ctot] replica of each carbon
   int* any;              // 1 if some replica rebuilds in this step
   int* abort;            // sticky: a bounded wait of a build gave up; no build runs until
@@ -204,6 +207,13 @@ __device__ __forceinline__ void record_grid(const Consts& K, const RepDesc& d, R
   s.scr_hi = (float)(K.rlist_sq + delta);
 }
 
+// The list build's work items before any brick is split (one thread).
+__device__ __forceinline__ void number_items(const Consts& K, const BuildArgs& A, int bricks) {
+  const int nbk = bricks + K.ntot / BRICK_NT <= K.ntot ? bricks : 0;
+  *A.nbk = nbk;
+  *A.nitems = nbk;
+}
+
 template <class MaxReduce>
 __device__ __forceinline__ bool decide_replica(const Consts& K, BuildArgs& A, int r, const double* dmax_tile,
                                                const double* tile_box, int force, int ppt, int t0, int tstep,
@@ -257,7 +267,7 @@ __global__ __launch_bounds__(DECIDE_THREADS) void k_decide(Consts K, BuildArgs A
       if (r < K.nrep) A.S[r].bk0 = carry + ex;
       carry += tot;
     }
-    if (threadIdx.x == 0) *A.nbk = carry;
+    if (threadIdx.x == 0) number_items(K, A, carry);
   }
   for (int r = threadIdx.x; r < K.nrep; r += DECIDE_THREADS) {   // builds are counted here
     RepState& s = A.S[r];
@@ -362,7 +372,7 @@ __device__ __forceinline__ void record_alike(const Consts& K, const BuildArgs& A
   if (g1.need) {
     s0.nbuilds += 1;
     s0.bk0 = 0;
-    *A.nbk = brick_count(s0.bn);
+    number_items(K, A, brick_count(s0.bn));
   }
 }
 
@@ -542,16 +552,62 @@ __global__ __launch_bounds__(BLOCK) void k_scan(BuildArgs A) {
   scan_chunk(A, b);
 }
 
+// The list build's work items of the bricks that tile lt of replica r takes: as many for a brick as
+// let a block's threads take an item's centers at once.  Bricks are cut for the replica's mean
+// density, and with vacuum in its grid (a film with a gap above it, a cluster, atoms far from a
+// surface) most are empty and the others hold several blocks' worth of centers.  A brick's first item
+// has the brick's number, so that neighbouring bricks run at the same time and find their windows in
+// the caches (in the order of an atomic counter the build over 14 A cells takes 1.13 of the time), and
+// the rest follow after all bricks.  Where there are more bricks than room for that, only the items
+// with centers are placed, by the counter (no more of them than atoms).  LG lanes count a brick's
+// centers, a cell row each.  Forced builds with one item per brick and with these: a 216k-atom slab
+// in a periodic box of four times its height 155 and 108 us, twenty atoms 200 A above it 157 and 112,
+// a cluster of 75k atoms in a box of 500 A 180 and 113; the film without vacuum is unchanged (k_scatter
+// 1 to 2 us longer, the list kernel as much shorter, as its blocks read an item in place of a count).
+__device__ __forceinline__ void list_items(const BuildArgs& A, const RepDesc& d, const RepState& S, int r, int lt) {
+  constexpr int LG = 8, ROWS = (BRICK_MAX * BRICK_MAX + LG - 1) / LG, PER = BLOCK / LG;
+  const int nb = brick_count(S.bn), sub = threadIdx.x % LG, own = *A.nbk > 0 ? 1 : 0;
+  const int none[3] = {0, 0, 0};
+  for (int l0 = lt * PER; l0 < nb; l0 += d.nt * PER) {   // uniform over the block
+    const int lb = l0 + threadIdx.x / LG;
+    int m = 0;
+    if (lb < nb && S.rebuild) {
+      const BrickHdr b = brick_geom(S.gd, S.bn, none, d.g0, lb);
+      const int ny = b.nry - 2, rows = ny * (b.nrows / b.nry - 2);
+      int from[ROWS], to[ROWS];
+#pragma unroll
+      for (int j = 0; j < ROWS; ++j) {   // all loads together (past the last row: that row's)
+        const int t = min(sub + j * LG, rows - 1), rz = t / ny;
+        const int* st = A.start + b.g0 + ((b.z0 + rz) * b.gy + b.y0 + (t - rz * ny)) * b.gx;
+        from[j] = st[b.x0];
+        to[j] = st[b.x1 + 1];
+      }
+#pragma unroll
+      for (int j = 0; j < ROWS; ++j) m += sub + j * LG < rows ? to[j] - from[j] : 0;
+    }
+#pragma unroll
+    for (int o = LG / 2; o > 0; o >>= 1) m += __shfl_xor(m, o, WAVE);
+    if (sub != 0 || lb >= nb) m = 0;
+    const int k = (m + BRICK_NT - 1) / BRICK_NT, more = max(k - own, 0);
+    const int incl = wave_scan(more), tot = __shfl(incl, WAVE - 1, WAVE);
+    int at = 0;
+    if (tot && threadIdx.x % WAVE == 0) at = atomicAdd(A.nitems, tot);
+    at = __shfl(at, 0, WAVE) + incl - more;
+    if (sub == 0 && lb < nb) {
+      if (own) A.items[S.bk0 + lb] = make_int4(r, lb, 0, k ? m / k : 0);
+      for (int j = own; j < k; ++j)
+        A.items[at++] = make_int4(r, lb, (int)((long long)m * j / k), (int)((long long)m * (j + 1) / k));
+    }
+  }
+}
+
 // Work item b of the scatter into cell order, as bin_item.
 __device__ __forceinline__ void scatter_item(const Consts& K, const BuildArgs& A, int b) {
-  for (int r = b; K.nrep > 1 && r < K.nrep; r += A.nbin) {   // the bricks' replicas
-    const int b0 = A.S[r].bk0, nb = brick_count(A.S[r].bn);
-    for (int t = threadIdx.x; t < nb; t += BLOCK) A.bk_rep[b0 + t] = r;
-  }
   if (b < A.ntiles) {
     const int r = A.tile_rep[b];
-    if (!A.S[r].rebuild) return;
     const RepDesc& d = A.R[r];
+    if (A.items) list_items(A, d, A.S[r], r, b - d.t0);
+    if (!A.S[r].rebuild) return;
     const int64_t i = (int64_t)b * TILE + threadIdx.x;
     if (i >= (int64_t)d.a0 + d.n) return;
     const int cid = A.cellid[i];
@@ -1051,7 +1107,8 @@ __device__ __forceinline__ void xlist_pass(const Consts& K, const BuildArgs& A, 
 }
 
 // Cr-Cr lists over bricks (replicas whose periodic axes all have >= 3 list cells).  A block
-// takes a brick (or one of `parts` shares of its centers), stages the brick's window in LDS as
+// takes a work item (a brick, or up to BRICK_NT of a crowded one's centers; see list_items) or one
+// of `parts` shares of its centers, stages the brick's window in LDS as
 // FP32 coordinates relative to the grid origin plus the image shift of the row and of the piece
 // across an x face, with the slot in the fourth word, and gives every center one lane.  A
 // center's candidates in one of its nine neighbouring cell rows (z-major, then y), x-cells
@@ -1094,20 +1151,23 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
     return;
   }
   const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
-  const int total = uniform(*A.nbk) * A.parts, nb = (int)gridDim.x - A.xblocks;
-  // (bricks in launch order: neighbouring ones on different XCDs, so that a batch's rebuilding
-  // replicas spread over the chip)
-  for (int u = (int)blockIdx.x - A.xblocks; u < total; u += nb) {
-    const int brick = A.parts == 1 ? u : u / A.parts, share = u - brick * A.parts;
-    const int r = K.nrep == 1 ? 0 : uniform(A.bk_rep[brick]);
+  const int nitems = uniform(*A.nitems), nbk = uniform(*A.nbk), nb = (int)gridDim.x - A.xblocks;
+  // (items in launch order: neighbouring bricks on different XCDs, so that a batch's rebuilding
+  // replicas spread over the chip; the further items of crowded bricks before all, as the last
+  // bricks may be a vacuum's)
+  for (int u = (int)blockIdx.x - A.xblocks; u < nitems * A.parts; u += nb) {
+    const int item = A.parts == 1 ? u : u / A.parts, share = u - item * A.parts;
+    const int4 it = A.items[item < nitems - nbk ? item + nbk : item - (nitems - nbk)];
+    const int r = uniform(it.x), i_lo = uniform(it.z), i_n = uniform(it.w) - i_lo;
+    const int c_lo = i_lo + i_n * share / A.parts, c_hi = i_lo + i_n * (share + 1) / A.parts;
+    if (c_lo >= c_hi) continue;   // uniform over the block
     RepState& S = A.S[r];
-    if (!uniform(S.rebuild)) continue;
     const RepDesc& d = A.R[r];
     const int per[3] = {uniform(d.per[0]), uniform(d.per[1]), uniform(d.per[2])};
     const double len0 = uniform(d.len[0]), len1 = uniform(d.len[1]), len2 = uniform(d.len[2]);
     const int sbase = uniform(d.a0 - A.start[d.g0]);   // sorted slot = sbase + start[cell]
-    __syncthreads();   // the previous brick's tables and stage are no longer read
-    if (wave == 0) brick_tables(brick_geom(S.gd, S.bn, per, d.g0, brick - S.bk0), per, A.start, sbase, tab);
+    __syncthreads();   // the previous item's tables, stage and counts are no longer read
+    if (wave == 0) brick_tables(brick_geom(S.gd, S.bn, per, d.g0, it.y), per, A.start, sbase, tab);
     __syncthreads();
     BrickHdr b;
     b.nry = uniform(tab.hdr.nry);
@@ -1121,9 +1181,7 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
     b.gz = uniform(tab.hdr.gz);
     b.xa = uniform(tab.hdr.xa);
     b.xb = uniform(tab.hdr.xb);
-    const int W = uniform(tab.roff[BRICK_ROWS]), m = uniform(tab.coff[BRICK_ROWS]);   // window, centers
-    const int c_lo = (int)((long long)m * share / A.parts), c_hi = (int)((long long)m * (share + 1) / A.parts);
-    if (c_lo >= c_hi) continue;   // uniform over the block
+    const int W = uniform(tab.roff[BRICK_ROWS]);   // atoms of the window
     constexpr int CW = 16;   // threads per row of the offsets (BRICK_CELLS of them work)
     static_assert(CW >= BRICK_CELLS, "a row's offsets");
     for (int e = threadIdx.x; e < b.nrows * CW; e += BRICK_NT) {
@@ -1151,12 +1209,12 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
     const unsigned band_bits = __float_as_uint(hi_f - lo_f);   // hi - lo, exact
     const float fxl = (float)(-len0), fxr = (float)len0;
     // lanes per center: as many (a power of two, up to 16) as let the threads take every center
-    // of this share at once
+    // of this share at once (an item has at most BRICK_NT)
     int gsh = 0;
     while (gsh < 4 && ((c_hi - c_lo) << (gsh + 1)) <= BRICK_NT) ++gsh;
-    const int G = 1 << gsh, gl = lane & (G - 1), NC = BRICK_NT >> gsh;
-    for (int c0 = c_lo; c0 < c_hi; c0 += NC) {
-      const int c = c0 + (threadIdx.x >> gsh);
+    const int G = 1 << gsh, gl = lane & (G - 1);
+    {
+      const int c = c_lo + (threadIdx.x >> gsh);
       const bool live = c < c_hi;
       const int crow = brick_center_row(tab, live ? c : c_lo);
       const int p = tab.cs[crow] + (live ? c : c_lo);
@@ -1166,8 +1224,8 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
       unsigned off = (unsigned)p * T;   // the next entry's place (one lane per center)
       for (int G0 = 0; G0 < W; G0 += LIST_STAGE) {   // uniform over the block
         const int nch = min(LIST_STAGE, W - G0);
-        if (c0 == c_lo || W > LIST_STAGE) {   // (else the one piece is still staged)
-          __syncthreads();   // the previous piece is no longer read
+        __syncthreads();   // the offsets are written; the previous piece is no longer read
+        {
           for (int row = wave; row < b.nrows; row += BRICK_NT / WAVE) {   // a row per wavefront
             const int ro = uniform(tab.roff[row]), nlm = uniform(tab.nlm[row]);
             const int g1 = min(uniform(tab.roff[row + 1]), G0 + nch) - ro;
@@ -1283,8 +1341,7 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
         if (count > cap) atomicMax(&S.overflow, count);
       }
       __syncthreads();
-      const int nc = min(NC, c_hi - c0);
-      if ((int)threadIdx.x < nc) {   // copy-back of the sorted state, one center per thread
+      if ((int)threadIdx.x < c_hi - c_lo) {   // copy-back of the sorted state, one center per thread
         const int p = psh[threadIdx.x], kept = csh[threadIdx.x];
         // all loads before the first store (a store could alias a later load, which would
         // then wait for it)
@@ -1297,7 +1354,7 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
         A.cnt[p] = kept;
         A.q[p] = pi;
         if (K.shadow) {
-          const int row = brick_center_row(tab, c0 + threadIdx.x);
+          const int row = brick_center_row(tab, c_lo + threadIdx.x);
           int uy, uz;
           brick_row(b, row, uy, uz);
           const long long bc = pack_cell(cell_coord(pi.x, uniform(S.glo[0]), uniform(S.ginv[0]), b.gx), uy, uz);
@@ -1318,7 +1375,6 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
         A.fixed[p] = fx;
         A.id[p] = ide;
       }
-      if (c0 + NC < c_hi) __syncthreads();   // the counts are no longer read
     }
   }
 }
