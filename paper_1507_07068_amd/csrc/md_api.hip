@@ -259,7 +259,28 @@ int xlist_blocks(const md_system* s) { return (morse_fused_blocks(s) + 1) / 2; }
 
 namespace {
 
-template <int T>
+// Calls f with the lanes per atom and the potential of the passes as integral constants, for the pairs
+// that occur (the paper's form has 4 or 8 lanes).
+template <class F>
+void with_lanes(const Consts& K, F f) {
+#define LANES(T, POT) f(std::integral_constant<int, T>{}, std::integral_constant<int, POT>{})
+#define PAPER_LANES(POT) \
+  if (K.ln == 4) LANES(4, POT); else LANES(8, POT)
+  if (K.pot == MD_POT_PAPER) {
+    if (K.P.bh > 0) { PAPER_LANES(POT_PAPER); } else { PAPER_LANES(POT_PAPER_POW); }
+  } else {
+    switch (K.ln) {
+      case 1: LANES(1, POT_FS); break;
+      case 2: LANES(2, POT_FS); break;
+      case 4: LANES(4, POT_FS); break;
+      default: LANES(8, POT_FS); break;
+    }
+  }
+#undef PAPER_LANES
+#undef LANES
+}
+
+template <int T, int POT>
 // morse: the leading blocks of the launch also run the Cr-C pass into fme (for a force
 // pass that adds it)
 void launch_density(md_system* s, const md_atoms* a, const md_lists* l, bool mixed, bool energy,
@@ -275,19 +296,15 @@ void launch_density(md_system* s, const md_atoms* a, const md_lists* l, bool mix
   int4* qs = qscur(s);
   double* dm = at<double>(s, s->L.dm);
   const int *li = pass_idx(s, l), *lc = pass_cnt(s, l);
-#define DENS(M_, SH, E, PA) \
-  k_density<T, M_, SH, E, PA><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, li, lc, rho_out, pe, M, dm)
-#define DENS_P(M_, SH, E) \
-  if (s->K.pot != MD_POT_PAPER) DENS(M_, SH, E, POT_FS);                     \
-  else if (s->K.P.bh > 0) DENS(M_, SH, E, POT_PAPER); else DENS(M_, SH, E, POT_PAPER_POW)
-  if (mixed && s->K.shadow && !s->list_mix) { if (energy) { DENS_P(true, true, true); } else { DENS_P(true, true, false); } }
-  else if (mixed) { if (energy) { DENS_P(true, false, true); } else { DENS_P(true, false, false); } }
-  else { if (energy) { DENS_P(false, false, true); } else { DENS_P(false, false, false); } }
-#undef DENS_P
+#define DENS(M_, SH, E) \
+  k_density<T, M_, SH, E, POT><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, li, lc, rho_out, pe, M, dm)
+  if (mixed && s->K.shadow && !s->list_mix) { if (energy) DENS(true, true, true); else DENS(true, true, false); }
+  else if (mixed) { if (energy) DENS(true, false, true); else DENS(true, false, false); }
+  else { if (energy) DENS(false, false, true); else DENS(false, false, false); }
 #undef DENS
 }
 
-template <int T>
+template <int T, int POT>
 // add_fme: the force includes the Cr-C force of this step from fme; full_kick: the kick is
 // dt a (the two half kicks of Task 5 and the next step's Task 3 at once), else dt a / 2;
 // drift (with full_kick or fuse_ke): the pass also drifts the atoms into the next position
@@ -310,26 +327,19 @@ void launch_force(md_system* s, const md_atoms* a, const md_lists* l, bool mixed
   const int nb = s->ntiles * T;
   const int4* qs = qscur(s);
   const double* dm = at<double>(s, s->L.dm);
-  const int pot = s->K.pot != MD_POT_PAPER ? POT_FS : s->K.P.bh > 0 ? POT_PAPER : POT_PAPER_POW;
   const int *li = pass_idx(s, l), *lc = pass_cnt(s, l);
-#define FORCE1(M, SH, KI, E, PA)                                                                                \
-  k_force<T, M, SH, KI, E, false, PA><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li,     \
+#define FORCE(M, SH, KI, E)                                                                                      \
+  k_force<T, M, SH, KI, E, false, POT><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li,    \
                                                              lc, pf, l->xcnt,                                    \
                                                              add_fme ? at<double>(s, s->L.fme) : nullptr, kick_h, D, dm, store_f, KO)
-#define FORCE(M, SH, KI, E) \
-  if (pot == POT_FS) FORCE1(M, SH, KI, E, POT_FS);                                                              \
-  else if (pot == POT_PAPER) FORCE1(M, SH, KI, E, POT_PAPER); else FORCE1(M, SH, KI, E, POT_PAPER_POW)
-#define FORCE_DRIFT1(M, SH, E, PA)                                                                               \
-  k_force<T, M, SH, true, E, true, PA><<<nb, BLOCK, 0, st>>>(                                                    \
+#define FORCE_DRIFT1(M, SH, E)                                                                                   \
+  k_force<T, M, SH, true, E, true, POT><<<nb, BLOCK, 0, st>>>(                                                   \
       s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li, lc, pf, l->xcnt,                                          \
       add_fme ? at<double>(s, s->L.fme) : nullptr, kick_h, D, dm, store_f, KO)
-#define FORCE_DRIFT2(M, SH, E) \
-  if (pot == POT_FS) FORCE_DRIFT1(M, SH, E, POT_FS);                                                            \
-  else if (pot == POT_PAPER) FORCE_DRIFT1(M, SH, E, POT_PAPER); else FORCE_DRIFT1(M, SH, E, POT_PAPER_POW)
 #define FORCE_DRIFT(M, SH) \
-  if (energy) { FORCE_DRIFT2(M, SH, true); } else { FORCE_DRIFT2(M, SH, false); }
+  if (energy) FORCE_DRIFT1(M, SH, true); else FORCE_DRIFT1(M, SH, false)
 #define FORCE_E(M, SH, KI) \
-  if (energy) { FORCE(M, SH, KI, true); } else { FORCE(M, SH, KI, false); }
+  if (energy) FORCE(M, SH, KI, true); else FORCE(M, SH, KI, false)
 #define FORCE_K(M, SH) \
   if (kick) { FORCE_E(M, SH, true); } else { FORCE_E(M, SH, false); }
   if (drift) {
@@ -340,12 +350,10 @@ void launch_force(md_system* s, const md_atoms* a, const md_lists* l, bool mixed
   else if (mixed) { FORCE_K(true, false); }
   else { FORCE_K(false, false); }
 #undef FORCE_DRIFT
-#undef FORCE_DRIFT2
 #undef FORCE_DRIFT1
 #undef FORCE_K
 #undef FORCE_E
 #undef FORCE
-#undef FORCE1
 }
 
 // add_f: the Cr-C forces are added into f (else only recorded in fme)
@@ -772,7 +780,7 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   // the Cr-C lists: leading blocks of the staged Cr-Cr list launch, else a launch of their own
   A.xblocks = (s->list_mix || s->ctot == 0) ? 0 : xlist_blocks(s);
   if (s->list_mix)
-    k_list_rows<false><<<s->ntiles, BLOCK, 0, st>>>(s->K, A);
+    k_list_rows<<<s->ntiles, BLOCK, 0, st>>>(s->K, A);
   else
     k_list_bricks<<<A.xblocks + list_blocks(s), BRICK_NT, 0, st>>>(s->K, A);
   if (ev1 && (e = hip_status(hipEventRecord(ev1, st)))) return e;
@@ -820,12 +828,7 @@ int eam_density(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
     const int e = inner_list(s, a, l, st, true);
     if (e) return e;
   }
-  switch (s->K.ln) {
-    case 1: launch_density<1>(s, a, l, mixed, energy, rho_out, morse, st); break;
-    case 2: launch_density<2>(s, a, l, mixed, energy, rho_out, morse, st); break;
-    case 4: launch_density<4>(s, a, l, mixed, energy, rho_out, morse, st); break;
-    default: launch_density<8>(s, a, l, mixed, energy, rho_out, morse, st); break;
-  }
+  with_lanes(s->K, [&](auto t, auto pot) { launch_density<t(), pot()>(s, a, l, mixed, energy, rho_out, morse, st); });
   s->have_embed = energy;
   return check_launch();
 }
@@ -835,12 +838,9 @@ int eam_density(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
 int eam_force(md_system* s, const md_atoms* a, const md_lists* l, uint32_t flags, bool add_fme, hipStream_t st,
               bool full_kick = false, bool drift = false, bool fuse_ke = false) {
   const bool mixed = flags & MD_F_MIXED, energy = flags & MD_F_ENERGY, kick = flags & MD_F_KICK;
-  switch (s->K.ln) {
-    case 1: launch_force<1>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke); break;
-    case 2: launch_force<2>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke); break;
-    case 4: launch_force<4>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke); break;
-    default: launch_force<8>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke); break;
-  }
+  with_lanes(s->K, [&](auto t, auto pot) {
+    launch_force<t(), pot()>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke);
+  });
   s->have_force = energy;
   return check_launch();
 }

@@ -91,10 +91,6 @@ struct BuildArgs {
   int spin_limit;        // polls of k_scan's look-back before it gives up (< 0: at once)
 };
 
-#ifndef MD_LIST_BATCH
-#define MD_LIST_BATCH 4
-#endif
-constexpr int LIST_BATCH = MD_LIST_BATCH;   // candidate loads issued together in k_list_rows
 constexpr int MAXC = 512;           // candidates staged per window in k_xlist
 #ifndef MD_SG_KEYS
 #define MD_SG_KEYS 8
@@ -193,8 +189,13 @@ __device__ __forceinline__ void record_grid(const Consts& K, const RepDesc& d, R
     s.gd[a] = g.gd[a];
   }
   s.qscale = g.qscale;
-  // the list build's FP32 screen (see k_list_rows): the staged coordinate includes the image
-  // shift, which the error bound covers (3 E)
+  // FP32 screen of the list build: r2f, the squared separation from FP32 coordinates relative to
+  // the grid origin (with the image shift), decides the pair when it lies outside
+  // [rl2 - delta, rl2 + delta); pairs inside that band get the exact FP64 test.  With u = 2^-24,
+  // coordinates within E of the origin and a periodic length L, each separation component
+  // carries an error of at most eta = u (3E + 2L + 3R) for |component| <= R = r_list + 1, so
+  // |r2f - r2| <= sum over axes of (2 R eta + eta^2) + 4 u (rl2 + R^2); delta is twice that.
+  // Pairs farther than R apart are far outside the band.
   const double u = 0x1p-24, R = K.rlist + 1.0;
   double err = 4.0 * u * (K.rlist_sq + R * R);
   for (int a = 0; a < 3; ++a) {
@@ -863,7 +864,6 @@ __global__ __launch_bounds__(BLOCK) void k_rebuild(Consts K, BuildArgs A, const 
 // (separation + 0 or -+ length: the same rounding as the minimum image for every pair
 // inside the list radius); along a periodic axis with fewer cells each cell is visited once
 // and the minimum image is taken pair by pair.
-template <bool SCREEN>
 __global__ __launch_bounds__(BLOCK) void k_list_rows(Consts K, BuildArgs A) {
   if (rebuild_off(A)) return;
   const int T = K.lt;
@@ -884,36 +884,11 @@ __global__ __launch_bounds__(BLOCK) void k_list_rows(Consts K, BuildArgs A) {
     const int sbase = d.a0 - A.start[d.g0];   // sorted slot = sbase + start[cell]
     const double rl2 = K.rlist_sq;
     const double4* __restrict__ tq = A.tq;
-    const float4* __restrict__ tqf = A.tqf;
     // entry k at idx[(k / T) * row + k % T]: wp walks the slots in entry order
     const int64_t row = K.ntot * T;
     int* __restrict__ wp = A.idx + (int64_t)p * T;
-    // pairwise minimum image on periodic axes with fewer than 3 cells (no FP32 screen then)
-    const bool mx = !SCREEN && d.per[0] && gx < 3, my = !SCREEN && d.per[1] && gy < 3,
-               mz = !SCREEN && d.per[2] && gz < 3;
-    // FP32 screen: r2f, the squared separation from FP32 coordinates relative to the grid
-    // origin, decides the pair when it lies outside [rl2 - delta, rl2 + delta); pairs inside
-    // that band get the exact FP64 test.  With u = 2^-24, coordinates within E of the origin
-    // and a periodic length L, each separation component carries an error of at most
-    // eta = u (2E + 2L + 3R) for |component| <= R = r_list + 1, so |r2f - r2| <= sum over axes
-    // of (2 R eta + eta^2) + 4 u (rl2 + R^2); delta is twice that.  Pairs farther than R
-    // apart are far outside the band.
-    float lo_f = 0.0f, hi_f = 0.0f;
-    if (SCREEN) {
-      const double u = 0x1p-24, R = K.rlist + 1.0;
-      const int g[3] = {gx, gy, gz};
-      double err = 4.0 * u * (rl2 + R * R);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const double E = g[a] / S.ginv[a] + 2.0 * R;
-        const double eta = u * (2.0 * E + (d.per[a] ? 2.0 * d.len[a] : 0.0) + 3.0 * R);
-        err += 2.0 * R * eta + eta * eta;
-      }
-      const double delta = 2.0 * err + 1e-6;
-      lo_f = (float)(rl2 - delta);
-      hi_f = (float)(rl2 + delta);
-    }
-    const float4 pf = SCREEN ? tqf[p] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    // pairwise minimum image on periodic axes with fewer than 3 cells
+    const bool mx = d.per[0] && gx < 3, my = d.per[1] && gy < 3, mz = d.per[2] && gz < 3;
     // x segments (first cell, last cell, shift), the same for every row
     int xa0 = cx - 1, xb0 = cx + 1, xa1 = 0, xb1 = -1;
     double sh0 = 0.0, sh1 = 0.0;
@@ -962,28 +937,8 @@ __global__ __launch_bounds__(BLOCK) void k_list_rows(Consts K, BuildArgs A) {
           ez = mz ? min_image(ez, d.len[2], d.half[2], 1) : ez + shz;
           return dist_sq_exact(ex, ey, ez) < rl2;
         };
-        if (SCREEN) {
-          const float fx = (float)shx, fy = (float)shy, fz = (float)shz;
-          auto test = [&](const float4& cf, int j) {
-            const float ex = (cf.x - pf.x) + fx, ey = (cf.y - pf.y) + fy, ez = (cf.z - pf.z) + fz;
-            const float r2f = ex * ex + ey * ey + ez * ez;
-            bool in = r2f < lo_f;
-            if (__builtin_expect(!in && !(r2f >= hi_f), 0)) in = exact(j);   // band (or NaN)
-            if (in && j != p) append(j);
-          };
-          int j = j0;
-          for (; j + LIST_BATCH <= j1; j += LIST_BATCH) {   // LIST_BATCH loads in flight
-            float4 cf[LIST_BATCH];
-#pragma unroll
-            for (int u = 0; u < LIST_BATCH; ++u) cf[u] = tqf[j + u];
-#pragma unroll
-            for (int u = 0; u < LIST_BATCH; ++u) test(cf[u], j + u);
-          }
-          for (; j < j1; ++j) test(tqf[j], j);
-        } else {
-          for (int j = j0; j < j1; ++j)
-            if (j != p && exact(j)) append(j);
-        }
+        for (int j = j0; j < j1; ++j)
+          if (j != p && exact(j)) append(j);
       }
     }
     A.cnt[p] = min(count, cap);
@@ -1113,8 +1068,8 @@ __device__ __forceinline__ void xlist_pass(const Consts& K, const BuildArgs& A, 
 // across an x face, with the slot in the fourth word, and gives every center one lane.  A
 // center's candidates in one of its nine neighbouring cell rows (z-major, then y), x-cells
 // cx-1 .. cx+1, are a contiguous range of window positions, so the candidate order (rows, along
-// x, by slot) is the same as in k_list_rows and the lists are identical.  The FP32 screen and its
-// exact FP64 band are those of k_list_rows.
+// x, by slot) is the same as in k_list_rows and the lists are identical.  An FP32 screen decides
+// all but a band around the list radius, which gets the exact FP64 test (see record_grid).
 //
 // A window over LIST_STAGE atoms is staged in pieces of that size.  Where a block's centers leave
 // threads over (large cells, a share of a brick), the lanes of a center take its candidates in
