@@ -121,8 +121,8 @@ typedef struct md_params {
     int32_t xcap;       /* Cr-C list capacity per atom */
     int32_t tpa;        /* lanes per atom in the density / force passes: 1, 2, 4 or 8 (the
                            Cr-Cr list is interleaved by tpa to match; cap must be a multiple
-                           of tpa); with MD_POT_PAPER, whose lists are long, 4 or 8 whatever
-                           the interleave (8 when tpa is 8) */
+                           of tpa); with MD_POT_PAPER more where that is faster: at least 4,
+                           or 8 for few atoms, over long lists, 2 or 4 over short ones */
     int32_t shadow;     /* 1: keep an FP32 copy of the positions relative to each atom's cell
                            (updated by the list build and md_verlet_step), from which the
                            MD_F_MIXED passes take their separations; 0: those passes round FP64

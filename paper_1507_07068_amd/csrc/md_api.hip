@@ -30,11 +30,16 @@ struct Layout {
 };
 
 constexpr int MISC_INTS = 16;    // rebuild flag, status words
-// The paper form's passes go over about 200 entries an atom, where 1 or 2 lanes leave few
-// wavefronts in flight and long chains in each: they take 4 lanes per atom, and 8 up to this many
-// atoms.  60 steps of a film, 8 against 4 lanes: 12,800 atoms 0.84 of the time, 41,000 0.97,
-// 52,000 the same, 80,000 1.05, 175,000 1.10.
-constexpr int64_t LANES8_ATOMS = 49152;
+// Lanes per atom of the paper form's passes: the more the longer the lists (1 or 2 lanes over the 200
+// entries of its own cutoff leave few wavefronts in flight and long chains in each) and the fewer
+// the atoms.  Over short lists 2, and 4 up to FEW_ATOMS; over longer ones 4, and 8 up to there.  Never
+// fewer than md_params.tpa.  Microseconds a step, FP64 / mixed, of a film with a cutoff for 14, 26, 50
+// and 64 entries: 216k atoms with 2 lanes 47 60 87 105 / 41 49 64 76, with 4 58 66 86 101 / 52 57 71
+// 78; 40k with 4 27 30 35 40 / 25 26 30 32, with 8 33 36 40 43 / 31 33 37 38; 10k with 4 19 20 24 27 /
+// 17 18 21 23, with 8 19 21 23 24 / 18 19 20 21.  Over the 206 entries, 8 against 4 lanes: 12,800
+// atoms 0.84 of the time, 41,000 0.97, 52,000 the same, 80,000 1.05, 175,000 1.10.
+constexpr int64_t FEW_ATOMS = 49152;
+constexpr double SHORT_ENTRIES = 40.0;
 // Two-tier lists: the middle lists' radius is r* (1 + MID_SKIN), 0.66 A of skin in the paper's
 // form.  They are taken again, at four times a refill, when an atom has moved half of that; 0.12
 // made each refill 7 % dearer, 0.05 no cheaper (the same lattice shells).
@@ -259,28 +264,32 @@ int xlist_blocks(const md_system* s) { return (morse_fused_blocks(s) + 1) / 2; }
 
 namespace {
 
-// Calls f with the lanes per atom and the potential of the passes as integral constants, for the pairs
-// that occur (the paper's form has 4 or 8 lanes).
+// Calls f with the passes' lanes per atom, potential and split of the sums as integral constants, for
+// the combinations that occur.
 template <class F>
 void with_lanes(const Consts& K, F f) {
-#define LANES(T, POT) f(std::integral_constant<int, T>{}, std::integral_constant<int, POT>{})
-#define PAPER_LANES(POT) \
-  if (K.ln == 4) LANES(4, POT); else LANES(8, POT)
+#define LANES(T, POT, H) \
+  f(std::integral_constant<int, T>{}, std::integral_constant<int, POT>{}, std::integral_constant<int, H>{})
+#define PAPER_LANES(POT)                   \
+  if (K.ln == 2) LANES(2, POT, 1);         \
+  else if (K.ln == 4 && K.split) LANES(4, POT, 1); \
+  else if (K.ln == 4) LANES(4, POT, 0);    \
+  else LANES(8, POT, 0)
   if (K.pot == MD_POT_PAPER) {
     if (K.P.bh > 0) { PAPER_LANES(POT_PAPER); } else { PAPER_LANES(POT_PAPER_POW); }
   } else {
     switch (K.ln) {
-      case 1: LANES(1, POT_FS); break;
-      case 2: LANES(2, POT_FS); break;
-      case 4: LANES(4, POT_FS); break;
-      default: LANES(8, POT_FS); break;
+      case 1: LANES(1, POT_FS, 0); break;
+      case 2: LANES(2, POT_FS, 0); break;
+      case 4: LANES(4, POT_FS, 0); break;
+      default: LANES(8, POT_FS, 0); break;
     }
   }
 #undef PAPER_LANES
 #undef LANES
 }
 
-template <int T, int POT>
+template <int T, int POT, int H>
 // morse: the leading blocks of the launch also run the Cr-C pass into fme (for a force
 // pass that adds it)
 void launch_density(md_system* s, const md_atoms* a, const md_lists* l, bool mixed, bool energy,
@@ -297,14 +306,14 @@ void launch_density(md_system* s, const md_atoms* a, const md_lists* l, bool mix
   double* dm = at<double>(s, s->L.dm);
   const int *li = pass_idx(s, l), *lc = pass_cnt(s, l);
 #define DENS(M_, SH, E) \
-  k_density<T, M_, SH, E, POT><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, li, lc, rho_out, pe, M, dm)
+  k_density<T, M_, SH, E, POT, H><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, li, lc, rho_out, pe, M, dm)
   if (mixed && s->K.shadow && !s->list_mix) { if (energy) DENS(true, true, true); else DENS(true, true, false); }
   else if (mixed) { if (energy) DENS(true, false, true); else DENS(true, false, false); }
   else { if (energy) DENS(false, false, true); else DENS(false, false, false); }
 #undef DENS
 }
 
-template <int T, int POT>
+template <int T, int POT, int H>
 // add_fme: the force includes the Cr-C force of this step from fme; full_kick: the kick is
 // dt a (the two half kicks of Task 5 and the next step's Task 3 at once), else dt a / 2;
 // drift (with full_kick or fuse_ke): the pass also drifts the atoms into the next position
@@ -329,11 +338,11 @@ void launch_force(md_system* s, const md_atoms* a, const md_lists* l, bool mixed
   const double* dm = at<double>(s, s->L.dm);
   const int *li = pass_idx(s, l), *lc = pass_cnt(s, l);
 #define FORCE(M, SH, KI, E)                                                                                      \
-  k_force<T, M, SH, KI, E, false, POT><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li,    \
+  k_force<T, M, SH, KI, E, false, POT, H><<<nb, BLOCK, 0, st>>>(s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li,    \
                                                              lc, pf, l->xcnt,                                    \
                                                              add_fme ? at<double>(s, s->L.fme) : nullptr, kick_h, D, dm, store_f, KO)
 #define FORCE_DRIFT1(M, SH, E)                                                                                   \
-  k_force<T, M, SH, true, E, true, POT><<<nb, BLOCK, 0, st>>>(                                                   \
+  k_force<T, M, SH, true, E, true, POT, H><<<nb, BLOCK, 0, st>>>(                                                   \
       s->K, R, S, tr, q, qs, a->v, a->f, a->fixed, li, lc, pf, l->xcnt,                                          \
       add_fme ? at<double>(s, s->L.fme) : nullptr, kick_h, D, dm, store_f, KO)
 #define FORCE_DRIFT(M, SH) \
@@ -548,8 +557,15 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   K.nrep = nrep;
   K.lt = p->tpa;
   K.lt_shift = p->tpa == 1 ? 0 : (p->tpa == 2 ? 1 : (p->tpa == 4 ? 2 : 3));
-  K.ln = p->tpa;   // (4 and 8 lanes give the same forces bit for bit: split_sums)
-  if (p->potential == MD_POT_PAPER) K.ln = std::max(p->tpa, s->ntot <= LANES8_ATOMS ? 8 : 4);
+  K.ln = p->tpa;
+  if (p->potential == MD_POT_PAPER) {
+    // (the passes read the inner list where there is one; each pair of lanes agrees bit for bit, as
+    // the smaller one splits its sums, and what picks the pair is the same for all replicas)
+    const double entries = std::min<double>(p->icap ? p->icap : p->cap, entries_within(*p, p->icap ? cut : rlist));
+    const int few = entries <= SHORT_ENTRIES ? 2 : 4;
+    K.ln = std::max(p->tpa, s->ntot <= FEW_ATOMS ? 2 * few : few);
+    K.split = K.ln == few ? 1 : 0;
+  }
   K.shadow = p->shadow ? 1 : 0;
   K.ntot = s->ntot;
   K.pot = p->potential;
@@ -828,7 +844,7 @@ int eam_density(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
     const int e = inner_list(s, a, l, st, true);
     if (e) return e;
   }
-  with_lanes(s->K, [&](auto t, auto pot) { launch_density<t(), pot()>(s, a, l, mixed, energy, rho_out, morse, st); });
+  with_lanes(s->K, [&](auto t, auto pot, auto h) { launch_density<t(), pot(), h()>(s, a, l, mixed, energy, rho_out, morse, st); });
   s->have_embed = energy;
   return check_launch();
 }
@@ -838,8 +854,8 @@ int eam_density(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
 int eam_force(md_system* s, const md_atoms* a, const md_lists* l, uint32_t flags, bool add_fme, hipStream_t st,
               bool full_kick = false, bool drift = false, bool fuse_ke = false) {
   const bool mixed = flags & MD_F_MIXED, energy = flags & MD_F_ENERGY, kick = flags & MD_F_KICK;
-  with_lanes(s->K, [&](auto t, auto pot) {
-    launch_force<t(), pot()>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke);
+  with_lanes(s->K, [&](auto t, auto pot, auto h) {
+    launch_force<t(), pot(), h()>(s, a, l, mixed, kick, energy, add_fme, st, full_kick, drift, fuse_ke);
   });
   s->have_force = energy;
   return check_launch();

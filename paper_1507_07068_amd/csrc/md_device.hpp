@@ -192,6 +192,7 @@ struct Consts {
   int lt;                 // list interleave: entries k..k+lt-1 of an atom are adjacent
   int lt_shift;           // log2(lt)
   int ln;                 // lanes per atom of the density and force passes (lt, or more for long lists)
+  int split;              // 1: those of the paper's form keep even and odd entries apart
   int shadow;             // 1: keep the FP32 cell-local shadow of the positions
   int pot;                // MD_POT_FS or MD_POT_PAPER
   int64_t ntot;           // atom slots (all replicas)

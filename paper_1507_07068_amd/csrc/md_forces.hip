@@ -31,11 +31,10 @@ __device__ __forceinline__ V group_sum(V v) {
 // list_slot / list_code), or body(fetch(e), e, m) with m of the right parity for the lane's
 // m-th entry.  Entries go U at a time: the U gathers of one group are in
 // flight together with the U index loads of the next.
-// The paper's form with 4 lanes per atom keeps a lane's even and odd entries apart (1: two sums,
-// picked by the entry's parity), so that its sums are, bit for bit, those of 8 lanes: the launch
-// may then pick 4 or 8 by the size of the whole batch, and a replica's forces still do not
-// depend on what it is batched with.
-__host__ __device__ constexpr int split_sums(int t, int pot) { return t == 4 && pot != POT_FS; }
+// H = 1 (the paper's form): a lane keeps its even and odd entries apart (two sums, picked by the
+// entry's parity), so that its sums are, bit for bit, those of twice the lanes with H = 0.  The launch
+// may then pick the lanes by the size of the whole batch, and a replica's forces still do not depend
+// on what it is batched with.
 
 // Left to itself the compiler fuses products and sums one way for the entries of a group and
 // another for those left over.  The paper form's pair terms say where they fuse, so that a pair
@@ -265,7 +264,7 @@ constexpr int PAPER_DENS_WAVES = 6;
 // relative cells; otherwise FP64 positions (rounded to FP32 for the MIXED arithmetic).
 // The paper's form (POT) -- rho_i = sum f, P_i = sum f^2, F'(rho_i) into q.w and M'(P_i)
 // into dm[i] (the second derivative of the paper's per-atom array).
-template <int T, bool MIXED, bool SHADOW, bool ENERGY, int POT = POT_FS>
+template <int T, bool MIXED, bool SHADOW, bool ENERGY, int POT, int H>
 __global__ __launch_bounds__(BLOCK, (POT == POT_PAPER && !MIXED) ? PAPER_DENS_WAVES : 1) void k_density(Consts K, const RepDesc* __restrict__ R,
                                                    RepState* __restrict__ S,
                                                    const int* __restrict__ tile_rep,
@@ -289,7 +288,6 @@ __global__ __launch_bounds__(BLOCK, (POT == POT_PAPER && !MIXED) ? PAPER_DENS_WA
   const double4 pi = (!SHADOW && c.live) ? q[c.i] : make_double4(0.0, 0.0, 0.0, 0.0);
   const bool img = !SHADOW && wave_near_face(d, c.live, pi.x, pi.y, pi.z, K.rlist + 2.0 * K.half_skin);
   double rho = 0.0, pp = 0.0;   // pp: P_i (paper's form)
-  constexpr int H = split_sums(T, POT);
   if (c.live) {
     const int64_t i = c.i;
     const int n = cnt[i];
@@ -476,7 +474,7 @@ struct SM {
 };
 
 // With the paper's form (POT) dm[j] = M'(P_j) from the density pass.
-template <int T, bool MIXED, bool SHADOW, bool KICK, bool ENERGY, bool DRIFT = false, int POT = POT_FS>
+template <int T, bool MIXED, bool SHADOW, bool KICK, bool ENERGY, bool DRIFT, int POT, int H>
 __global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && POT == POT_FS) ? MD_FORCE_KIN_WAVES : MD_FORCE_WAVES) void k_force(Consts K, const RepDesc* __restrict__ R,
                                                  RepState* __restrict__ S,
                                                  const int* __restrict__ tile_rep,
@@ -510,7 +508,6 @@ __global__ __launch_bounds__(BLOCK, (ENERGY && DRIFT && POT == POT_FS) ? MD_FORC
       // Horner in x = r / re; all lanes evaluate and the cutoffs select, with F'_j and M'_j
       // used on every path (so the neighbour's record is loaded ahead of the arithmetic)
       const PaperConsts& P = K.P;
-      constexpr int H = split_sums(T, POT);
       if (MIXED) {
         const float rcs = (float)P.rc_sq, phs = (float)P.phi_sq, ire = (float)P.inv_re, dd = (float)P.d,
                     b0 = (float)P.b0, b1 = (float)P.b1, b2 = (float)P.b2, b3 = (float)P.b3, beta = (float)P.beta;
