@@ -137,9 +137,10 @@ typedef struct md_params {
                            largest Cr-Cr cutoff; the passes then read the inner list.  0: one
                            list, read by the passes */
     md_eam_paper_params paper;
-    int32_t list_tgt;   /* atoms a work item of the Cr-Cr list build aims at (a launch-shape
-                           choice, 32 .. 256; 0: 224): from 224 down, a brick of cells is shared
-                           by 224 / list_tgt blocks; results do not depend on it */
+    int32_t list_tgt;   /* launch shape of the Cr-Cr list build, 32 .. 256 (0: 224): below 107 each
+                           of its work items (a brick of cells) is shared by 160 / list_tgt
+                           blocks; else by one, or up to 8 where the system's bricks alone would
+                           not fill the chip; results do not depend on it */
     int32_t pad;
 } md_params;
 

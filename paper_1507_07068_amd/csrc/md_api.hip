@@ -90,7 +90,9 @@ struct md_system {
   // grid of the build kernels that stride over their tiles (set at bind from the device)
   int tile_grid = 2048;
   int cus = 256;
-  int list_parts = 1;    // blocks per brick in the list build that md_params.list_tgt asks for
+  int list_parts = 0;    // blocks per work item of the list build that md_params.list_tgt asks for (0: none)
+  int list_grid = 0;     // blocks of the list build that MD_LIST_PERSISTENT in the environment at
+                         // creation asks for (0: list_blocks decides; results do not depend on it)
   int static_dev = -1;   // device whose static scratch is the workspace (md_workspace_bind_static)
 };
 
@@ -235,10 +237,11 @@ int scan_spin_limit() {
   return e ? std::atoi(e) : (1 << 22);
 }
 
-// Blocks that share a brick in the list build: as list_tgt asks for, or enough that a small
-// system's bricks fill the compute units.
+// Blocks that share a work item of the list build: as list_tgt asks for, else enough (up to 8) that a
+// small system's bricks fill the compute units.
 int list_parts(const md_system* s) {
-  return (int)std::max<int64_t>(s->list_parts, std::min<int64_t>(8, s->cus / std::max<int64_t>(1, s->best)));
+  if (s->list_parts) return s->list_parts;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(8, s->cus / std::max<int64_t>(1, s->best)));
 }
 // Blocks of the list build: about as many as there are shares of work items (their number is known on
 // the device; the blocks stride over them), up to LIST_WAVES times what the chip holds (three of
@@ -247,6 +250,7 @@ int list_parts(const md_system* s) {
 // block per share, 7.65 at 16 times the chip, 7.84 at 8, 8.28 at 4, 9.30 at 2 (uneven shares).
 constexpr int LIST_WAVES = 16;
 int list_blocks(const md_system* s) {
+  if (s->list_grid > 0) return s->list_grid;
   return (int)std::min<int64_t>((std::max<int64_t>(s->best + s->best / 4, s->ntot / 400) + 8) * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
 }
 
@@ -423,8 +427,11 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   s->ws = nullptr;
   s->have_embed = s->have_force = false;
   s->list_mix = false;
-  // list_tgt: a brick (about 400 centers) whole at the default 224, shared by more blocks below
-  s->list_parts = p->list_tgt ? std::max(1, (224 + p->list_tgt / 2) / p->list_tgt) : 1;
+  // list_tgt: items (about 400 centers) shared by more than one block below 107.  A share stages the
+  // whole window, so that these are fewer blocks than 400 / list_tgt: forced builds of the 64-replica
+  // ensemble with 1, 2, 3, 5 blocks 271, 331, 377, 490 us (run-sized items of 64 atoms took 395).
+  s->list_parts = p->list_tgt ? (160 + p->list_tgt / 2) / p->list_tgt : 0;
+  if (s->list_parts == 1) s->list_parts = 0;
   s->bcap = s->best = 0;
   // the list holds pairs within the potential's largest Cr-Cr cutoff + skin
   const double cut = p->potential == MD_POT_PAPER ? std::max(p->paper.rc, p->paper.d * p->paper.re) : p->eam.c;
@@ -589,6 +596,8 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
   {
     const char* fe = std::getenv("MD_FUSE_ENERGY");
     s->fuse_energy = !(fe && std::atoi(fe) == 0);
+    const char* lp = std::getenv("MD_LIST_PERSISTENT");
+    s->list_grid = lp ? std::min(std::max(std::atoi(lp), 0), 1 << 20) : 0;
   }
   s->L = make_layout(*s);
   *out = s;

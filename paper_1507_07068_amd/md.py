@@ -200,7 +200,8 @@ class Simulation:
         cell-local positions for the FP32-mixed passes (default: when precision is mixed).
         icap: two-tier lists (Section 2.6) with this inner-list capacity per atom; the
         Cr-Cr list of capacity cap is then the outer list (give the system the outer skin).
-        list_tgt: below 224, each brick of the list build goes to 224 / list_tgt blocks (0: one).
+        list_tgt: below 107, each brick of the list build goes to 160 / list_tgt blocks (else the
+        library decides).
         static_workspace: bind the library's static device scratch (md_workspace_bind_static)
         instead of a workspace tensor."""
         import torch

@@ -3,12 +3,12 @@
 Two shape parameters change speed but not results:
 
 * ``tpa``: the lanes that share one atom in the density and force passes (1, 2, 4 or 8; the
-  list is interleaved to match; the paper's form, whose lists are long, takes 4 or 8 whatever
-  the interleave).  Few lanes per atom leave long serial gathers; many lanes
+  list is interleaved to match; the paper's form takes more by the length of its lists and the
+  number of atoms, so that small values differ in the interleave alone there).  Few lanes per atom leave long serial gathers; many lanes
   spend more on the cross-lane reduction and on idle lanes of short lists.
-* ``list_tgt``: below 224 the list build gives each brick of cells to 224 / ``list_tgt`` blocks,
-  which spreads a rebuild over more of them (good for many small replicas); from 224 on one
-  block stages a brick for all its centres.
+* ``list_tgt``: below 107 the list build gives each brick of cells to 160 / ``list_tgt`` blocks,
+  which spreads a rebuild over more of them; from there on the library decides (one block per
+  brick, more for systems whose bricks would not fill the chip).
 
 The best choice depends on the list lengths, on the atoms a launch has to fill the chip with,
 and on how often lists are rebuilt, so it is measured.  Each candidate runs a short stretch of
@@ -27,7 +27,7 @@ import time
 
 _CACHE: dict = {}
 TPA = (1, 2, 4, 8)
-LIST_TGT = (128, 160, 224)
+LIST_TGT = (32, 64, 224)   # 5, 3 blocks per brick, and the library's choice
 DEFAULT_LIST_TGT = 224
 
 

@@ -82,3 +82,30 @@ def test_batch_in_which_some_rebuild():
         assert nb[0] == builds[r]
         for k in ("x", "v", "f", "dF"):
             assert np.array_equal(alone[0][k], both[r][k]), (r, k)
+
+
+@pytest.mark.parametrize("list_tgt", [0, 64])
+@pytest.mark.parametrize("batch", [False, True])
+def test_few_blocks_stride_over_the_items(batch, list_tgt, monkeypatch):
+    """1 and 3 blocks that take item after item, of several replicas that rebuild in different steps,
+    against a block per share: lists and trajectories bit for bit."""
+    reps = [slab(14, 13, 8, 5.0, 61, temperature=4000.0)]
+    if batch:
+        reps += [dimers(300, 300.0, 62), I.bulk(7, seed=63, temperature=50.0),
+                 I.small_film(nx=12, ny=11, nz=6, radius=6.0, gap=0.5, seed=64)]
+    out = []
+    for blocks in ("0", "1", "3"):
+        monkeypatch.setenv("MD_LIST_PERSISTENT", blocks)
+        print(f"[case] items blocks={blocks} {[s.n for s in reps]} list_tgt={list_tgt}", flush=True)
+        sim = md.Simulation(reps, tpa=2, xcap=160, list_tgt=list_tgt)
+        sim.initial_forces()
+        sim.md_run(25)
+        st = sim.md_check()
+        assert not (st["overflow"] or st["xoverflow"] or st["nonfinite"] or st["sync_timeout"]), st
+        rows = [sim.neighbor_sets(r) for r in range(len(reps))]
+        out.append((sim.state(), rows, [sim.neighbor_sets(r, cross=True) for r in range(len(reps))], st))
+    for state, rows, cross, st in out[1:]:
+        assert rows == out[0][1] and cross == out[0][2] and st == out[0][3]
+        for r in range(len(reps)):
+            for k in ("x", "v", "f", "dF"):
+                assert np.array_equal(state[r][k], out[0][0][r][k]), (r, k)
