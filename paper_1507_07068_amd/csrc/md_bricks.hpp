@@ -73,27 +73,28 @@ struct BrickTab {
   int rw[BRICK_ROWS];         // cell 0 of the row (-1: outside an open axis, or past the rows)
 };
 
-// First cell of brick i of an axis of g cells cut into bn bricks, which the first g % bn of them
-// share out (nothing here grows past g, so 32 bits hold axes of any length).
-__host__ __device__ inline int brick_first(int i, int g, int bn) {
-  const int left = g % bn;
-  return i * (g / bn) + (i < left ? i : left);
+// First cell of brick i of an axis of g cells cut into bn bricks of q = g / bn cells, the first g % bn
+// of them one more (nothing here grows past g, so 32 bits hold axes of any length).
+__host__ __device__ inline int brick_first(int i, int q, int g, int bn) {
+  const int left = g - q * bn;
+  return i * q + (i < left ? i : left);
 }
 
 // Brick lb of a replica with grid gd cut into bn bricks.
-__host__ __device__ inline BrickHdr brick_geom(const int (&gd)[3], const int (&bn)[3], const int (&per)[3], int g0, int lb) {
+__host__ __device__ inline BrickHdr brick_geom(const int (&gd)[3], const int (&bn)[3], const int (&bq)[3], const int (&per)[3],
+                                               int g0, int lb) {
   BrickHdr b;
   b.gx = gd[0];
   b.gy = gd[1];
   b.gz = gd[2];
   b.g0 = g0;
   const int ix = lb % bn[0], iy = lb / bn[0] % bn[1], iz = lb / (bn[0] * bn[1]);
-  b.x0 = brick_first(ix, b.gx, bn[0]);
-  b.x1 = brick_first(ix + 1, b.gx, bn[0]) - 1;
-  b.y0 = brick_first(iy, b.gy, bn[1]);
-  b.z0 = brick_first(iz, b.gz, bn[2]);
-  b.nry = brick_first(iy + 1, b.gy, bn[1]) - b.y0 + 2;
-  b.nrows = b.nry * (brick_first(iz + 1, b.gz, bn[2]) - b.z0 + 2);
+  b.x0 = brick_first(ix, bq[0], b.gx, bn[0]);
+  b.x1 = brick_first(ix + 1, bq[0], b.gx, bn[0]) - 1;
+  b.y0 = brick_first(iy, bq[1], b.gy, bn[1]);
+  b.z0 = brick_first(iz, bq[2], b.gz, bn[2]);
+  b.nry = brick_first(iy + 1, bq[1], b.gy, bn[1]) - b.y0 + 2;
+  b.nrows = b.nry * (brick_first(iz + 1, bq[2], b.gz, bn[2]) - b.z0 + 2);
   b.xa = b.x0 > 0 ? b.x0 - 1 : 0;
   b.xb = b.x1 + 1 < b.gx ? b.x1 + 1 : b.gx - 1;
   b.flags = (per[0] && b.x0 == 0 ? BRICK_WL : 0) | (per[0] && b.x1 == b.gx - 1 ? BRICK_WR : 0);

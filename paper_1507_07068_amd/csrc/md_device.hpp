@@ -55,6 +55,7 @@ struct alignas(64) RepState {
   double qscale;          // fixed-point scale of the shadow positions (a power of two)
   int gd[3];
   int bn[3];              // bricks along each axis (see choose_bricks)
+  int bq[3];              // cells along a brick's edge at least: gd / bn
   int bk0;                // its first brick in the launch-wide numbering
   float scr_lo, scr_hi;   // band of the list build's FP32 screen
 };

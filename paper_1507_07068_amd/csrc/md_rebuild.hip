@@ -179,6 +179,7 @@ __device__ __forceinline__ void record_grid(const Consts& K, const RepDesc& d, R
   s.rebuild = g.need;
   if (!g.need) return;
   choose_bricks(d.n, d.bcap, g.gd, s.bn);
+  for (int a = 0; a < 3; ++a) s.bq[a] = g.gd[a] / s.bn[a];
   s.mid_ok = 0;
   s.nnear_old = s.nnear;
   s.nnear = 0;
@@ -568,20 +569,24 @@ __global__ __launch_bounds__(BLOCK) void k_scan(BuildArgs A) {
 __device__ __forceinline__ void list_items(const BuildArgs& A, const RepDesc& d, const RepState& S, int r, int lt) {
   constexpr int LG = 8, ROWS = (BRICK_MAX * BRICK_MAX + LG - 1) / LG, PER = BLOCK / LG;
   const int nb = brick_count(S.bn), sub = threadIdx.x % LG, own = *A.nbk > 0 ? 1 : 0;
-  const int none[3] = {0, 0, 0};
+  const int gx = S.gd[0], gy = S.gd[1];
   for (int l0 = lt * PER; l0 < nb; l0 += d.nt * PER) {   // uniform over the block
     const int lb = l0 + threadIdx.x / LG;
     int m = 0;
     if (lb < nb && S.rebuild) {
-      const BrickHdr b = brick_geom(S.gd, S.bn, none, d.g0, lb);
-      const int ny = b.nry - 2, rows = ny * (b.nrows / b.nry - 2);
+      const int iyz = lb / S.bn[0], ix = lb - iyz * S.bn[0], iz = iyz / S.bn[1], iy = iyz - iz * S.bn[1];
+      const int x0 = brick_first(ix, S.bq[0], gx, S.bn[0]), x1 = brick_first(ix + 1, S.bq[0], gx, S.bn[0]);
+      const int y0 = brick_first(iy, S.bq[1], gy, S.bn[1]), ny = brick_first(iy + 1, S.bq[1], gy, S.bn[1]) - y0;
+      const int z0 = brick_first(iz, S.bq[2], S.gd[2], S.bn[2]);
+      const int rows = ny * (brick_first(iz + 1, S.bq[2], S.gd[2], S.bn[2]) - z0);
+      const float inv = 1.0f / (float)ny;
       int from[ROWS], to[ROWS];
 #pragma unroll
       for (int j = 0; j < ROWS; ++j) {   // all loads together (past the last row: that row's)
-        const int t = min(sub + j * LG, rows - 1), rz = t / ny;
-        const int* st = A.start + b.g0 + ((b.z0 + rz) * b.gy + b.y0 + (t - rz * ny)) * b.gx;
-        from[j] = st[b.x0];
-        to[j] = st[b.x1 + 1];
+        const int t = min(sub + j * LG, rows - 1), rz = (int)(((float)t + 0.5f) * inv);
+        const int* st = A.start + d.g0 + ((z0 + rz) * gy + y0 + (t - rz * ny)) * gx;
+        from[j] = st[x0];
+        to[j] = st[x1];
       }
 #pragma unroll
       for (int j = 0; j < ROWS; ++j) m += sub + j * LG < rows ? to[j] - from[j] : 0;
@@ -590,10 +595,12 @@ __device__ __forceinline__ void list_items(const BuildArgs& A, const RepDesc& d,
     for (int o = LG / 2; o > 0; o >>= 1) m += __shfl_xor(m, o, WAVE);
     if (sub != 0 || lb >= nb) m = 0;
     const int k = (m + BRICK_NT - 1) / BRICK_NT, more = max(k - own, 0);
-    const int incl = wave_scan(more), tot = __shfl(incl, WAVE - 1, WAVE);
     int at = 0;
-    if (tot && threadIdx.x % WAVE == 0) at = atomicAdd(A.nitems, tot);
-    at = __shfl(at, 0, WAVE) + incl - more;
+    if (__any(more > 0)) {   // (no brick of most films)
+      const int incl = wave_scan(more);
+      if (threadIdx.x % WAVE == WAVE - 1) at = atomicAdd(A.nitems, incl);
+      at = __shfl(at, WAVE - 1, WAVE) + incl - more;
+    }
     if (sub == 0 && lb < nb) {
       if (own) A.items[S.bk0 + lb] = make_int4(r, lb, 0, k ? m / k : 0);
       for (int j = own; j < k; ++j)
@@ -1122,7 +1129,7 @@ __global__ __launch_bounds__(BRICK_NT, MD_LIST_WAVES) void k_list_bricks(Consts 
     const double len0 = uniform(d.len[0]), len1 = uniform(d.len[1]), len2 = uniform(d.len[2]);
     const int sbase = uniform(d.a0 - A.start[d.g0]);   // sorted slot = sbase + start[cell]
     __syncthreads();   // the previous item's tables, stage and counts are no longer read
-    if (wave == 0) brick_tables(brick_geom(S.gd, S.bn, per, d.g0, it.y), per, A.start, sbase, tab);
+    if (wave == 0) brick_tables(brick_geom(S.gd, S.bn, S.bq, per, d.g0, uniform(it.y)), per, A.start, sbase, tab);
     __syncthreads();
     BrickHdr b;
     b.nry = uniform(tab.hdr.nry);

@@ -22,13 +22,14 @@ int main() {
     int bn[3];
     const int per[3] = {1, 1, 1};
     md::choose_bricks(n, cap, gd, bn);
+    const int bq[3] = {gd[0] / bn[0], gd[1] / bn[1], gd[2] / bn[2]};
     const char* bad = nullptr;
     if ((long long)bn[0] * bn[1] * bn[2] > cap) bad = "capacity";
     int next[3] = {0, 0, 0};
     for (int a = 0; a < 3 && !bad; ++a) {
       const long long step = a == 0 ? 1 : a == 1 ? bn[0] : (long long)bn[0] * bn[1];
       for (int i = 0; i < bn[a] && !bad; ++i) {
-        const md::BrickHdr b = md::brick_geom(gd, bn, per, 0, (int)(i * step));
+        const md::BrickHdr b = md::brick_geom(gd, bn, bq, per, 0, (int)(i * step));
         const int first = a == 0 ? b.x0 : a == 1 ? b.y0 : b.z0;
         const int cells = a == 0 ? b.x1 - b.x0 + 1 : a == 1 ? b.nry - 2 : b.nrows / b.nry - 2;
         if (first != next[a]) bad = "first cell";
