@@ -187,7 +187,7 @@ Layout make_layout(const md_system& s) {
   L.midx = take(s.mid_cap ? sizeof(int) * n * (size_t)s.mid_cap : 0);
   L.mcnt = take(s.mid_cap ? sizeof(int) * n : 0);
   L.mref = take(s.mid_cap ? sizeof(float) * 4 * n : 0);
-  L.msum = take(s.mid_cap ? sizeof(unsigned long long) * n : 0);
+  L.msum = take(s.mid_cap ? sizeof(ulonglong2) * n : 0);
   L.total = s.mid_cap ? o : L.base;
   return L;
 }
@@ -834,7 +834,7 @@ int inner_list(md_system* s, const md_atoms* a, const md_lists* l, hipStream_t s
   const double4* q = qcur(s, a);
   float4* qf = at<float4>(s, s->L.tqf);
   const MidList M{s->mid ? at<int>(s, s->L.midx) : nullptr, at<int>(s, s->L.mcnt), at<float4>(s, s->L.mref),
-                  at<unsigned long long>(s, s->L.msum), s->mid_cap};
+                  at<ulonglong2>(s, s->L.msum), s->mid_cap};
   const int nm = grid_tiles(s) * MID_G;
   k_inner_pos<<<grid_tiles(s), BLOCK, 0, st>>>(s->K, R, S, tr, q, qf, M);
   if (s->mid && first)
