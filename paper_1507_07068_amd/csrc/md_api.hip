@@ -248,10 +248,14 @@ int list_parts(const md_system* s) {
 // its blocks per compute unit).  A step without a rebuild pays for dispatching them all: 12.9 us
 // (now 7.3) for the 26,000 shares of an 8M-atom film.  Ten steps of it, list launches in all: 7.98 ms with a
 // block per share, 7.65 at 16 times the chip, 7.84 at 8, 8.28 at 4, 9.30 at 2 (uneven shares).
+// The bricks expected are those of the boxes given, which may be higher than the atoms reach (an
+// indenter above a film), and then cut into larger bricks than the build finds; so no fewer blocks
+// than one per 256 atoms either (items have 300 to 500): 308 blocks for the 330 items of a
+// 101k-atom film made the last ones wait for a second round, 108 us a forced build against 97.
 constexpr int LIST_WAVES = 16;
 int list_blocks(const md_system* s) {
   if (s->list_grid > 0) return s->list_grid;
-  return (int)std::min<int64_t>((std::max<int64_t>(s->best + s->best / 4, s->ntot / 400) + 8) * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
+  return (int)std::min<int64_t>((std::max<int64_t>(s->best + s->best / 4, s->ntot / 256) + 8) * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
 }
 
 // Grid of the kernels that walk the near-indenter atoms (one wavefront per atom, grid-stride).
