@@ -24,7 +24,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Byte offsets of the workspace regions.
 struct Layout {
-  size_t desc, state, tile_rep, c_rep, misc, sync, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
+  size_t desc, state, tile_rep, c_rep, misc, sync, bt_rep, chunks, chunk_out, xref, dmax, tbox, cellid, crank, perm, skey, tq, tqf, qs, q2, qs2, bcell, tv,
       tf, tfixed, tid, count, start, hcell, hrank, hlist, hsorted, scan_state, hnear, near, fme, p_embed, p_force,
       p_morse, p_kin, dm, dmax_p, tbox_p, base, midx, mcnt, mref, msum, total;
 };
@@ -65,6 +65,7 @@ struct md_system {
   std::vector<RepDesc> desc;
   std::vector<int> tile_rep;
   std::vector<int> c_rep;
+  std::vector<int> bt_rep;     // replica of each group of bricks
   std::vector<int2> chunks;    // energy sums: (first tile, tile count) of each chunk
   int64_t ntot, ctot;
   int ntiles;
@@ -145,6 +146,7 @@ Layout make_layout(const md_system& s) {
   L.c_rep = take(sizeof(int) * (size_t)s.ctot);
   L.misc = take(sizeof(int) * MISC_INTS);
   L.sync = take(sizeof(int) * SYNC_INTS);
+  L.bt_rep = take(s.nrep > 1 ? sizeof(int) * s.bt_rep.size() : 0);
   L.chunks = take(sizeof(int2) * s.chunks.size());
   L.chunk_out = take(sizeof(double) * 16 * s.chunks.size());
   L.xref = take(sizeof(double) * 3 * n);
@@ -255,7 +257,8 @@ int list_parts(const md_system* s) {
 constexpr int LIST_WAVES = 16;
 int list_blocks(const md_system* s) {
   if (s->list_grid > 0) return s->list_grid;
-  return (int)std::min<int64_t>((std::max<int64_t>(s->best + s->best / 4, s->ntot / 256) + 8) * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
+  const int64_t items = std::min<int64_t>(std::max<int64_t>(s->best + s->best / 4, s->ntot / 256) + 8, s->ntot);
+  return (int)std::min<int64_t>(items * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
 }
 
 // Grid of the kernels that walk the near-indenter atoms (one wavefront per atom, grid-stride).
@@ -493,7 +496,12 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
       int gd[3], bn[3];
       for (int a = 0; a < 3; ++a) gd[a] = cells_along(rd.len[a], rlist);
       choose_bricks(rd.n, dd.bcap, gd, bn);
-      s->best += std::min<int64_t>(dd.bcap, (int64_t)bn[0] * bn[1] * bn[2]);
+      const int64_t best = std::min<int64_t>(dd.bcap, (int64_t)bn[0] * bn[1] * bn[2]);
+      s->best += best;
+      // (more bricks than expected: a group strides over further ones)
+      dd.bt0 = (int)s->bt_rep.size();
+      dd.nbt = (int)((best + best / 4) / BRICK_GROUP) + 1;
+      s->bt_rep.insert(s->bt_rep.end(), (size_t)dd.nbt, r);
       if (s->bcap > (int64_t)INT32_MAX / 16) { delete s; return MD_ERR_ARG; }
     }
     s->desc.back().ch0 = (int)s->chunks.size();
@@ -639,6 +647,9 @@ int bind_workspace(md_system* s, void* ws, size_t bytes, hipStream_t st) {
   if ((e = hip_status(hipMemcpyAsync(at<int>(s, s->L.tile_rep), s->tile_rep.data(),
                                      sizeof(int) * s->ntiles, hipMemcpyHostToDevice, st))))
     return e;
+  if (s->nrep > 1 && (e = hip_status(hipMemcpyAsync(at<int>(s, s->L.bt_rep), s->bt_rep.data(),
+                                                    sizeof(int) * s->bt_rep.size(), hipMemcpyHostToDevice, st))))
+    return e;
   if (s->ctot > 0 &&
       (e = hip_status(hipMemcpyAsync(at<int>(s, s->L.c_rep), s->c_rep.data(), sizeof(int) * s->ctot,
                                      hipMemcpyHostToDevice, st))))
@@ -718,6 +729,8 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   A.nitems = misc + 2;
   A.nbk = misc + 4;
   A.parts = list_parts(s);
+  A.bt_rep = at<int>(s, s->L.bt_rep);
+  A.nbt = s->list_mix ? 0 : (int)s->bt_rep.size();
   A.c_rep = at<int>(s, s->L.c_rep);
   A.any = misc + 0;
   A.abort = misc + 3;
@@ -776,7 +789,7 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   const int64_t bin_blocks = tgrid, nparts = (int64_t)s->ntiles * s->ppt;
   const bool decide_in_bin = !(flags & MD_B_FORCE) && s->K.nrep == 1;
   A.commit_ref = decide_in_bin ? 1 : 0;
-  const bool fused = A.nbin <= REBUILD_ITEMS;   // (then the parts are few too)
+  const bool fused = A.nbin <= REBUILD_ITEMS && A.scan_blocks <= A.nbin;   // (then the parts are few too)
   if (fused && decide_in_bin) {
     k_rebuild<true><<<tgrid, BLOCK, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
                                              (int)nparts);
@@ -801,7 +814,7 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   }
   if (!fused) {
     k_scan<<<s->scan_blocks, BLOCK, 0, st>>>(A);
-    k_scatter<<<tgrid, BLOCK, 0, st>>>(s->K, A);
+    k_scatter<<<std::min(A.nbt + A.nbin, s->tile_grid), BLOCK, 0, st>>>(s->K, A);
     k_sort_gather<<<tgrid, BLOCK, 0, st>>>(s->K, A);
   }
   int e;

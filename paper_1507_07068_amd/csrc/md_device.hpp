@@ -28,6 +28,7 @@ struct RepDesc {
                         // use along open axes follow the atoms, see RepState)
   int h0, hd[3];        // Cr-C cell grid: first cell (global, after all Cr grids), dims
   int bcap;             // bricks at capacity
+  int bt0, nbt;         // groups of bricks that list the build's work items: first, count
   int ch0, nch;         // energy sums: first chunk of tiles, chunk count
   double ginv[3];       // cells per Angstrom of the Cr grid along periodic axes
   double hinv[3];       // cells per Angstrom of the carbon grid

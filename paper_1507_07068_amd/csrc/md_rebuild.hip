@@ -79,7 +79,9 @@ struct BuildArgs {
   int* near;             // [ntot]: replica r's near atoms at near[a0_r ...]
   double* fme;           // [ntot][4]: last Morse force and energy per atom (0 if none)
   int ncell_all, ncell_cr, ntiles, ctot;
-  int parts;             // blocks that share a brick in the list build
+  const int* bt_rep;     // [nbt] replica of each group of bricks (several replicas only)
+  int nbt;               // groups of bricks (see list_items)
+  int parts;             // blocks that share a work item in the list build
   int nbin;              // tile blocks' worth of work of k_bin, k_scatter, k_sort_gather: the Cr
                          // tiles, then 256-carbon groups (the grids stride over them)
   int near_blocks;       // grid of k_xlist
@@ -262,12 +264,20 @@ __global__ __launch_bounds__(DECIDE_THREADS) void k_decide(Consts K, BuildArgs A
   if (threadIdx.x == 0) *A.any = any_sh;
   if (any_sh) {   // launch-wide numbering of the bricks
     int carry = 0;
-    for (int r0 = 0; r0 < K.nrep; r0 += DECIDE_THREADS) {
-      const int r = r0 + threadIdx.x;
-      int tot;
-      const int ex = block_exclusive_scan<DECIDE_THREADS>(r < K.nrep ? brick_count(A.S[r].bn) : 0, &tot);
-      if (r < K.nrep) A.S[r].bk0 = carry + ex;
-      carry += tot;
+    if (K.nrep <= WAVE) {
+      if (threadIdx.x < WAVE) {
+        const int r = threadIdx.x, c = r < K.nrep ? brick_count(A.S[r].bn) : 0, incl = wave_scan(c);
+        if (r < K.nrep) A.S[r].bk0 = incl - c;
+        carry = __shfl(incl, WAVE - 1, WAVE);
+      }
+    } else {
+      for (int r0 = 0; r0 < K.nrep; r0 += DECIDE_THREADS) {
+        const int r = r0 + threadIdx.x;
+        int tot;
+        const int ex = block_exclusive_scan<DECIDE_THREADS>(r < K.nrep ? brick_count(A.S[r].bn) : 0, &tot);
+        if (r < K.nrep) A.S[r].bk0 = carry + ex;
+        carry += tot;
+      }
     }
     if (threadIdx.x == 0) number_items(K, A, carry);
   }
@@ -554,23 +564,27 @@ __global__ __launch_bounds__(BLOCK) void k_scan(BuildArgs A) {
   scan_chunk(A, b);
 }
 
-// The list build's work items of the bricks that tile lt of replica r takes: as many for a brick as
-// let a block's threads take an item's centers at once.  Bricks are cut for the replica's mean
-// density, and with vacuum in its grid (a film with a gap above it, a cluster, atoms far from a
-// surface) most are empty and the others hold several blocks' worth of centers.  A brick's first item
-// has the brick's number, so that neighbouring bricks run at the same time and find their windows in
-// the caches (in the order of an atomic counter the build over 14 A cells takes 1.13 of the time), and
-// the rest follow after all bricks.  Where there are more bricks than room for that, only the items
-// with centers are placed, by the counter (no more of them than atoms).  LG lanes count a brick's
-// centers, a cell row each.  Forced builds with one item per brick and with these: a 216k-atom slab
-// in a periodic box of four times its height 155 and 108 us, twenty atoms 200 A above it 157 and 112,
-// a cluster of 75k atoms in a box of 500 A 180 and 113; the film without vacuum is unchanged (k_scatter
-// 1 to 2 us longer, the list kernel as much shorter, as its blocks read an item in place of a count).
-__device__ __forceinline__ void list_items(const BuildArgs& A, const RepDesc& d, const RepState& S, int r, int lt) {
-  constexpr int LG = 8, ROWS = (BRICK_MAX * BRICK_MAX + LG - 1) / LG, PER = BLOCK / LG;
+// The list build's work items of group j of the bricks: as many for a brick as let a block's threads
+// take an item's centers at once.  Bricks are cut for the replica's mean density, and with vacuum in
+// its grid (a film with a gap above it, a cluster, atoms far from a surface) most are empty and the
+// others hold several blocks' worth of centers.  A brick's first item has the brick's number, so that
+// neighbouring bricks run at the same time and find their windows in the caches (in the order of an
+// atomic counter the build over 14 A cells takes 1.13 of the time), and the rest follow after all
+// bricks.  Where there are more bricks than room for that, only the items with centers are placed, by
+// the counter (no more of them than atoms).  LG lanes count a brick's centers, a cell row each.
+// Forced builds with one item per brick and with these: a 216k-atom slab in a periodic box of four
+// times its height 155 and 108 us, twenty atoms 200 A above it 157 and 112, a cluster of 75k atoms in
+// a box of 500 A 180 and 113; films without vacuum the same (the list kernel's blocks read an item in
+// place of a count).
+constexpr int BRICK_GROUP = 32;   // bricks per group
+__device__ __forceinline__ void list_items(const Consts& K, const BuildArgs& A, int j) {
+  constexpr int LG = BLOCK / BRICK_GROUP, ROWS = (BRICK_MAX * BRICK_MAX + LG - 1) / LG;
+  const int r = K.nrep == 1 ? 0 : A.bt_rep[j];
+  const RepDesc& d = A.R[r];
+  const RepState& S = A.S[r];
   const int nb = brick_count(S.bn), sub = threadIdx.x % LG, own = *A.nbk > 0 ? 1 : 0;
   const int gx = S.gd[0], gy = S.gd[1];
-  for (int l0 = lt * PER; l0 < nb; l0 += d.nt * PER) {   // uniform over the block
+  for (int l0 = (j - d.bt0) * BRICK_GROUP; l0 < nb; l0 += d.nbt * BRICK_GROUP) {   // uniform over the block
     const int lb = l0 + threadIdx.x / LG;
     int m = 0;
     if (lb < nb && S.rebuild) {
@@ -613,9 +627,8 @@ __device__ __forceinline__ void list_items(const BuildArgs& A, const RepDesc& d,
 __device__ __forceinline__ void scatter_item(const Consts& K, const BuildArgs& A, int b) {
   if (b < A.ntiles) {
     const int r = A.tile_rep[b];
-    const RepDesc& d = A.R[r];
-    if (A.items) list_items(A, d, A.S[r], r, b - d.t0);
     if (!A.S[r].rebuild) return;
+    const RepDesc& d = A.R[r];
     const int64_t i = (int64_t)b * TILE + threadIdx.x;
     if (i >= (int64_t)d.a0 + d.n) return;
     const int cid = A.cellid[i];
@@ -668,7 +681,10 @@ __device__ __forceinline__ void scatter_item(const Consts& K, const BuildArgs& A
 
 __global__ __launch_bounds__(BLOCK) void k_scatter(Consts K, BuildArgs A) {
   if (rebuild_off(A)) return;
-  for (int b = blockIdx.x; b < A.nbin; b += gridDim.x) scatter_item(K, A, b);   // (b uniform over the block)
+  for (int b = blockIdx.x; b < A.nbt + A.nbin; b += gridDim.x) {   // (b uniform over the block)
+    if (b < A.nbt) list_items(K, A, b);
+    else scatter_item(K, A, b - A.nbt);
+  }
 }
 
 // One lane per slot in cell order.  Work item b < ntiles: a tile of Cr slots; else 256 carbon
@@ -766,7 +782,8 @@ __global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
 }
 
 // k_bin, k_scan, k_scatter and k_sort_gather in one launch, for systems of few work items
-// (at most REBUILD_ITEMS).  A step without a rebuild, most of a run's, then pays for one launch
+// (at most REBUILD_ITEMS) and no more chunks of cells than that (the holders of the items scan them:
+// 250 atoms strewn over 400 A, 419 chunks for one block, took 1.39 ms a build against 0.14).  A step without a rebuild, most of a run's, then pays for one launch
 // that finds nothing to do in place of four (about 2 us each, beside passes of 8 to 20 us).
 // Blocks take the binning's items from a counter and keep them for the later phases, each of
 // which waits for the end of the one before: only blocks that hold items keep another back, and
@@ -786,6 +803,10 @@ constexpr int REBUILD_ITEMS = 48;
 // up, as a scan that does; scan: or one of its chunks did).
 __device__ __forceinline__ bool phase_end(const BuildArgs& A, int* done, int mine, int items, bool scan = false) {
   __shared__ int ok_sh;
+  if (mine == items && gridDim.x == 1) {   // (a system of one item: no other block's stores to wait for)
+    __syncthreads();
+    return !scan || __hip_atomic_load(A.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+  }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // each thread's stores of this phase
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -851,7 +872,10 @@ __global__ __launch_bounds__(BLOCK) void k_rebuild(Consts K, BuildArgs A, const 
       }
   // (a scan that gave up: nothing is scattered, and the counters stay until md_clear_flags)
   if (!phase_end(A, A.sync + SY_SCAN * SYNC_STRIDE, chunks, A.scan_blocks, true)) return;
-  for (int k = 0; k < n; ++k) scatter_item(K, A, own[k]);
+  for (int k = 0; k < n; ++k) {
+    for (int j = own[k]; j < A.nbt; j += A.nbin) list_items(K, A, j);
+    scatter_item(K, A, own[k]);
+  }
   if (!phase_end(A, A.sync + SY_SCATTER * SYNC_STRIDE, n, A.nbin)) return;
   for (int k = 0; k < n; ++k) sort_item(K, A, own[k]);
   // the last block to leave, when every block has decided and looked for its last item, records

@@ -30,7 +30,7 @@ def dimers(n, box, seed):
 
 
 @pytest.mark.parametrize("tpa,precision", [(1, "fp64"), (4, "mixed")])
-@pytest.mark.parametrize("kind", ["slab", "open", "dilute"])
+@pytest.mark.parametrize("kind", ["slab", "open", "dilute", "one_tile", "one_launch"])
 def test_lists(kind, tpa, precision):
     if kind == "slab":
         s = slab(24, 22, 12, 6.0, 51)
@@ -38,8 +38,12 @@ def test_lists(kind, tpa, precision):
         s = I.film(24, 22, 12, 0.0, 0.0, 52, noise=0.05)
         s.x[np.nonzero(s.fixed == 0)[0][::997], 2] += 300.0
         s.box_len = s.box_len + np.array([0.0, 0.0, 300.0])
-    else:                  # 4,000 bricks, 512 slots
+    elif kind == "dilute":     # 4,000 bricks, 512 slots
         s = dimers(400, 400.0, 53)
+    elif kind == "one_tile":   # 419 chunks of cells, one tile of atoms
+        s = dimers(200, 400.0, 59)
+    else:                      # as many chunks as tiles: still rebuilt in one launch
+        s = dimers(3000, 120.0, 60)
     print(f"[case] items {kind} n={s.n} tpa={tpa} {precision}", flush=True)
     sim = md.Simulation(s, tpa=tpa, precision=precision)
     sim.md_build_neighbors(force=True)
