@@ -252,12 +252,12 @@ int list_parts(const md_system* s) {
 // block per share, 7.65 at 16 times the chip, 7.84 at 8, 8.28 at 4, 9.30 at 2 (uneven shares).
 // The bricks expected are those of the boxes given, which may be higher than the atoms reach (an
 // indenter above a film), and then cut into larger bricks than the build finds; so no fewer blocks
-// than one per 256 atoms either (items have 300 to 500): 308 blocks for the 330 items of a
+// than one per 300 atoms either (items have 300 to 500): 308 blocks for the 330 items of a
 // 101k-atom film made the last ones wait for a second round, 108 us a forced build against 97.
 constexpr int LIST_WAVES = 16;
 int list_blocks(const md_system* s) {
   if (s->list_grid > 0) return s->list_grid;
-  const int64_t items = std::min<int64_t>(std::max<int64_t>(s->best + s->best / 4, s->ntot / 256) + 8, s->ntot);
+  const int64_t items = std::min<int64_t>(std::max<int64_t>(s->best + s->best / 4, s->ntot / 300) + 8, s->ntot);
   return (int)std::min<int64_t>(items * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
 }
 
@@ -789,9 +789,11 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   const int64_t bin_blocks = tgrid, nparts = (int64_t)s->ntiles * s->ppt;
   const bool decide_in_bin = !(flags & MD_B_FORCE) && s->K.nrep == 1;
   A.commit_ref = decide_in_bin ? 1 : 0;
-  const bool fused = A.nbin <= REBUILD_ITEMS && A.scan_blocks <= A.nbin;   // (then the parts are few too)
+  const bool fused = A.nbin <= REBUILD_ITEMS && A.scan_blocks <= REBUILD_CHUNKS;   // (then the parts are few too)
+  A.nrb = std::max(A.nbin, std::min(REBUILD_ITEMS, std::max(A.scan_blocks, A.nbt)));
+  const int rgrid = std::min(A.nrb, s->tile_grid);
   if (fused && decide_in_bin) {
-    k_rebuild<true><<<tgrid, BLOCK, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
+    k_rebuild<true><<<rgrid, BLOCK, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
                                              (int)nparts);
   } else if (decide_in_bin && bin_blocks * nparts <= DECIDE_IN_BIN_MAX_LOADS) {
     k_bin<true><<<tgrid, BLOCK, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
@@ -808,7 +810,7 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
     k_decide<<<1, DECIDE_THREADS, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),
                                   (flags & MD_B_FORCE) ? 1 : 0, (flags & MD_B_FORCE) ? 1 : s->ppt);
     if (fused)
-      k_rebuild<false><<<tgrid, BLOCK, 0, st>>>(s->K, A, nullptr, nullptr, 0);
+      k_rebuild<false><<<rgrid, BLOCK, 0, st>>>(s->K, A, nullptr, nullptr, 0);
     else
       k_bin<false><<<tgrid, BLOCK, 0, st>>>(s->K, A, nullptr, nullptr, 0);
   }

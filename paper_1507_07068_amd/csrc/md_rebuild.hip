@@ -84,6 +84,7 @@ struct BuildArgs {
   int parts;             // blocks that share a work item in the list build
   int nbin;              // tile blocks' worth of work of k_bin, k_scatter, k_sort_gather: the Cr
                          // tiles, then 256-carbon groups (the grids stride over them)
+  int nrb;               // k_rebuild's work items: nbin, or more where there are more chunks to scan
   int near_blocks;       // grid of k_xlist
   int xblocks;           // leading blocks of k_list_bricks that build the Cr-C lists (0: none)
   int commit_ref;        // k_scan records the indenter position of this build (k_bin decided)
@@ -782,8 +783,10 @@ __global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
 }
 
 // k_bin, k_scan, k_scatter and k_sort_gather in one launch, for systems of few work items
-// (at most REBUILD_ITEMS) and no more chunks of cells than that (the holders of the items scan them:
-// 250 atoms strewn over 400 A, 419 chunks for one block, took 1.39 ms a build against 0.14).  A step without a rebuild, most of a run's, then pays for one launch
+// (at most REBUILD_ITEMS; at most REBUILD_CHUNKS chunks of cells).  The holders of the items scan the
+// chunks and list the bricks' work items too, so a system of few atoms in many cells gets more items
+// than it has atoms for (250 atoms strewn over 400 A, 419 chunks: 1.39 ms a forced build with one
+// item, 116 us with 48; four launches 57 us, but 18 against 12 us a step without a rebuild).  A step without a rebuild, most of a run's, then pays for one launch
 // that finds nothing to do in place of four (about 2 us each, beside passes of 8 to 20 us).
 // Blocks take the binning's items from a counter and keep them for the later phases, each of
 // which waits for the end of the one before: only blocks that hold items keep another back, and
@@ -798,6 +801,7 @@ constexpr int PHASE_SPINS = 1 << 22;
 // four launches: 1,024 atoms 0.89 of the time (cold) and 0.94 (melting, a rebuild every few
 // steps), 8,192 atoms 0.90 and 0.97, 16,000 0.96 and 1.06.
 constexpr int REBUILD_ITEMS = 48;
+constexpr int REBUILD_CHUNKS = 512;
 
 // Counts the block's `mine` items of a phase of `items` and waits for the others' (false: given
 // up, as a scan that does; scan: or one of its chunks did).
@@ -851,7 +855,7 @@ __global__ __launch_bounds__(BLOCK) void k_rebuild(Consts K, BuildArgs A, const 
     if (threadIdx.x == 0) own[n] = atomicAdd(A.sync + SY_TAKEN * SYNC_STRIDE, 1);
     __syncthreads();
     const int b = own[n];
-    if (b >= A.nbin) break;
+    if (b >= A.nrb) break;
     ++n;
     if (b == 0) {   // (the record and the scan's fresh state are part of the phase)
       if (DECIDE && threadIdx.x == 0) record_alike(K, A, g1);
@@ -859,11 +863,11 @@ __global__ __launch_bounds__(BLOCK) void k_rebuild(Consts K, BuildArgs A, const 
     }
     bin_item<DECIDE>(K, A, g1, b);
   }
-  if (!phase_end(A, A.sync + SY_BIN * SYNC_STRIDE, n, A.nbin)) return;
+  if (!phase_end(A, A.sync + SY_BIN * SYNC_STRIDE, n, A.nrb)) return;
   // the scan's chunks go to the holders of the items of the same number (modulo their count); a
   // holder takes its chunks in ascending order, so the lowest unfinished one is always under way
   int chunks = 0;
-  for (int c0 = 0; c0 < A.scan_blocks; c0 += A.nbin)
+  for (int c0 = 0; c0 < A.scan_blocks; c0 += A.nrb)
     for (int k = 0; k < n; ++k)
       if (c0 + own[k] < A.scan_blocks) {
         scan_chunk(A, c0 + own[k]);
@@ -873,10 +877,10 @@ __global__ __launch_bounds__(BLOCK) void k_rebuild(Consts K, BuildArgs A, const 
   // (a scan that gave up: nothing is scattered, and the counters stay until md_clear_flags)
   if (!phase_end(A, A.sync + SY_SCAN * SYNC_STRIDE, chunks, A.scan_blocks, true)) return;
   for (int k = 0; k < n; ++k) {
-    for (int j = own[k]; j < A.nbt; j += A.nbin) list_items(K, A, j);
+    for (int j = own[k]; j < A.nbt; j += A.nrb) list_items(K, A, j);
     scatter_item(K, A, own[k]);
   }
-  if (!phase_end(A, A.sync + SY_SCATTER * SYNC_STRIDE, n, A.nbin)) return;
+  if (!phase_end(A, A.sync + SY_SCATTER * SYNC_STRIDE, n, A.nrb)) return;
   for (int k = 0; k < n; ++k) sort_item(K, A, own[k]);
   // the last block to leave, when every block has decided and looked for its last item, records
   // the indenter position and clears the counters for the next build
