@@ -807,17 +807,14 @@ constexpr int REBUILD_CHUNKS = 512;
 // up, as a scan that does; scan: or one of its chunks did).
 __device__ __forceinline__ bool phase_end(const BuildArgs& A, int* done, int mine, int items, bool scan = false) {
   __shared__ int ok_sh;
-  if (mine == items && gridDim.x == 1) {   // (a system of one item: no other block's stores to wait for)
-    __syncthreads();
-    return !scan || __hip_atomic_load(A.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // each thread's stores of this phase
+  const bool alone = gridDim.x == 1;   // (a system of one item: no other block's stores to wait for)
+  if (!alone) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // each thread's stores of this phase
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (mine) atomicAdd(done, mine);
+    if (mine && !alone) atomicAdd(done, mine);
     int spins = 0;
     bool ok = true;
-    while (ok && __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < items) {
+    while (ok && !alone && __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < items) {
       if (++spins > PHASE_SPINS) {
         A.S[0].sync_timeout = 1;
         *A.any = 0;
@@ -830,7 +827,7 @@ __device__ __forceinline__ bool phase_end(const BuildArgs& A, int* done, int min
     ok_sh = ok ? 1 : 0;
   }
   __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the other blocks' stores
+  if (!alone) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the other blocks' stores
   const bool ok = ok_sh != 0;
   __syncthreads();   // (ok_sh is free again)
   return ok;
