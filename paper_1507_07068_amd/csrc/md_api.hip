@@ -790,7 +790,7 @@ int build_chain(md_system* s, const md_atoms* a, const md_lists* l, uint32_t fla
   const bool decide_in_bin = !(flags & MD_B_FORCE) && s->K.nrep == 1;
   A.commit_ref = decide_in_bin ? 1 : 0;
   const bool fused = A.nbin <= REBUILD_ITEMS && A.scan_blocks <= REBUILD_CHUNKS;   // (then the parts are few too)
-  A.nrb = std::max(A.nbin, std::min(REBUILD_ITEMS, std::max(A.scan_blocks, A.nbt)));
+  A.nrb = std::max(A.nbin, std::min(REBUILD_ITEMS, std::max(A.scan_blocks, A.nbin + A.nbt)));
   const int rgrid = std::min(A.nrb, s->tile_grid);
   if (fused && decide_in_bin) {
     k_rebuild<true><<<rgrid, BLOCK, 0, st>>>(s->K, A, at<double>(s, s->L.dmax), at<double>(s, s->L.tbox),

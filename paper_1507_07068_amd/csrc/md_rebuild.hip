@@ -84,7 +84,7 @@ struct BuildArgs {
   int parts;             // blocks that share a work item in the list build
   int nbin;              // tile blocks' worth of work of k_bin, k_scatter, k_sort_gather: the Cr
                          // tiles, then 256-carbon groups (the grids stride over them)
-  int nrb;               // k_rebuild's work items: nbin, or more where there are more chunks to scan
+  int nrb;               // k_rebuild's work items: nbin, and more for the bricks and the scan
   int near_blocks;       // grid of k_xlist
   int xblocks;           // leading blocks of k_list_bricks that build the Cr-C lists (0: none)
   int commit_ref;        // k_scan records the indenter position of this build (k_bin decided)
@@ -784,8 +784,8 @@ __global__ __launch_bounds__(BLOCK) void k_sort_gather(Consts K, BuildArgs A) {
 
 // k_bin, k_scan, k_scatter and k_sort_gather in one launch, for systems of few work items
 // (at most REBUILD_ITEMS; at most REBUILD_CHUNKS chunks of cells).  The holders of the items scan the
-// chunks and list the bricks' work items too, so a system of few atoms in many cells gets more items
-// than it has atoms for (250 atoms strewn over 400 A, 419 chunks: 1.39 ms a forced build with one
+// chunks and list the bricks' work items too, so there are more items than the binning's: one per
+// group of bricks, and as many as chunks (250 atoms strewn over 400 A, 419 chunks: 1.39 ms a forced build with one
 // item, 116 us with 48; four launches 57 us, but 18 against 12 us a step without a rebuild).  A step without a rebuild, most of a run's, then pays for one launch
 // that finds nothing to do in place of four (about 2 us each, beside passes of 8 to 20 us).
 // Blocks take the binning's items from a counter and keep them for the later phases, each of
@@ -874,7 +874,8 @@ __global__ __launch_bounds__(BLOCK) void k_rebuild(Consts K, BuildArgs A, const 
   // (a scan that gave up: nothing is scattered, and the counters stay until md_clear_flags)
   if (!phase_end(A, A.sync + SY_SCAN * SYNC_STRIDE, chunks, A.scan_blocks, true)) return;
   for (int k = 0; k < n; ++k) {
-    for (int j = own[k]; j < A.nbt; j += A.nrb) list_items(K, A, j);
+    // (the groups of bricks to the items past the binning's first, which have nothing to scatter)
+    for (int j = own[k] >= A.nbin ? own[k] - A.nbin : own[k] - A.nbin + A.nrb; j < A.nbt; j += A.nrb) list_items(K, A, j);
     scatter_item(K, A, own[k]);
   }
   if (!phase_end(A, A.sync + SY_SCATTER * SYNC_STRIDE, n, A.nrb)) return;
