@@ -278,8 +278,8 @@ MD_API int md_build_neighbors(md_system *sys, const md_atoms *a, const md_lists 
  * pass.  With MD_F_KICK the Task 5 half kick v += F/m dt/2 of the whole force follows
  * (mobile atoms).  MD_F_MIXED selects FP32 arithmetic.  Lists must be current
  * (md_build_neighbors in the same step).  With two-tier lists (icap > 0) MD_F_DENSITY first
- * refills the inner list from the outer one at the current positions (Section 2.6, Task 1:
- * the inner list is updated every step), and both passes read it. */
+ * refills the inner list from the outer one given, at the current positions (Section 2.6, Task
+ * 1: the inner list is updated every step), and both passes read it. */
 MD_API int md_eam_forces(md_system *sys, const md_atoms *a, const md_lists *l, uint32_t flags,
                          double *rho_out, void *stream);
 

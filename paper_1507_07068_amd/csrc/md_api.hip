@@ -247,8 +247,8 @@ int list_parts(const md_system* s) {
 }
 // Blocks of the list build: about as many as there are shares of work items (their number is known on
 // the device; the blocks stride over them), up to LIST_WAVES times what the chip holds (three of
-// its blocks per compute unit).  A step without a rebuild pays for dispatching them all: 12.9 us
-// (now 7.3) for the 26,000 shares of an 8M-atom film.  Ten steps of it, list launches in all: 7.98 ms with a
+// its blocks per compute unit).  A step without a rebuild pays for dispatching them all: 13 us
+// for the 26,000 shares of an 8M-atom film, 7 with the limit.  Ten steps of it, list launches in all: 7.98 ms with a
 // block per share, 7.65 at 16 times the chip, 7.84 at 8, 8.28 at 4, 9.30 at 2 (uneven shares).
 // The bricks expected are those of the boxes given, which may be higher than the atoms reach (an
 // indenter above a film), and then cut into larger bricks than the build finds; so no fewer blocks

@@ -1,4 +1,4 @@
-// Bricks of the cell grid and their windows (gfx950): the work items of the list build.
+// Bricks of the cell grid and their windows (gfx950), from which the list build takes its work items.
 //
 // A brick is a block of neighbouring cells of the sorted order; its window is those cells and
 // one layer around them, as cell rows (z, then y), each the atoms of x-cells x0-1 .. x1+1 in

@@ -61,8 +61,8 @@ struct alignas(64) RepState {
   float scr_lo, scr_hi;   // band of the list build's FP32 screen
 };
 
-// The cell grid is cut into bricks (blocks of neighbouring cells, a few hundred atoms): the
-// list build takes one brick per block, and its window -- the brick's cells and one layer
+// The cell grid is cut into bricks (blocks of neighbouring cells, a few hundred atoms): a block of
+// the list build takes a brick, or part of a crowded one, and its window -- the brick's cells and one layer
 // around them -- is staged in LDS.
 struct BrickHdr {         // one brick: its cells and its window's rows
   int nry, nrows;         // window rows along y, in all

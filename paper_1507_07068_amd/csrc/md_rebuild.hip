@@ -7,16 +7,20 @@
 //   k_scan          exclusive scan of all cell counts (one pass, decoupled look-back)
 //   k_scatter       atom slots / carbon indices into their cells at the ranks k_bin took
 //                   (arbitrary order within a cell), with the (cell, id) sort keys; marks
-//                   the 27-cell stencil of every occupied carbon cell
+//                   the 27-cell stencil of every occupied carbon cell; lists the list build's
+//                   work items (list_items)
 //   k_sort_gather   one lane per slot: rank within its cell by (cell, id), gather the atom
 //                   state into sorted order (so the final order is canonical); atoms in a
 //                   marked carbon cell join the near list
-//   k_list_bricks   one block per brick of cells (md_bricks.hpp): the brick's window is staged
-//                   in LDS, each atom scans its nine cell rows of it; copies the sorted state
-//                   back.  Its leading blocks build the Cr-C lists (xlist_pass: one
+//   k_rebuild       those four as phases of one launch (small systems)
+//   k_list_bricks   one block per work item, a brick of cells (md_bricks.hpp) or part of a crowded
+//                   one: the brick's window is staged in LDS, each atom scans its nine cell rows
+//                   of it; copies the sorted state back.  Its leading blocks build the Cr-C lists (xlist_pass: one
 //                   wavefront per near atom).  k_list_rows (one lane per atom from global
 //                   memory, for periodic axes with fewer than 3 cells) is followed by
 //                   k_xlist, the same Cr-C pass as a launch of its own.
+//   k_inner_pos, k_mid_check, k_mid_list, k_inner_list   two-tier lists: the inner lists refilled
+//                   every step from the outer ones, by way of middle lists where those pay
 //
 // Every build kernel after the decision returns at once when no replica needs a rebuild, so
 // a step without a rebuild costs a few empty launches.
@@ -1108,13 +1112,13 @@ __device__ __forceinline__ void xlist_pass(const Consts& K, const BuildArgs& A, 
 // threads over (large cells, a share of a brick), the lanes of a center take its candidates in
 // runs and place their entries after a prefix over the lanes.
 //
-// Bound by VALU work (about 0.7 of the issue slots; the screen and the append loop), with the
-// partly filled lines of the entry stores behind it.  Against one block per run of cells of a
-// single cell row, which staged nine windows' worth of atoms per center instead of 3.4 and had
-// one lane per center (us per rebuild): 174 against 198 on the 1M-atom film, 50 against 62 on
-// the 216k-atom one, 460 against 620 with the paper's form, 1.4 against 4.9 ms for its outer
-// lists, 65 against 240 on the 10k-atom film, 19 against 38 on a 2k-atom bulk; even on the
-// 8M-atom film (1.30 ms).  Held to 6 wavefronts per SIMD (three blocks per compute unit): at 5
+// Bound by VALU work (0.86 of the issue slots on the 8M-atom film, 0.82 on the 1M-atom one; the
+// screen and the append loop), with the partly filled lines of the entry stores behind it.  Against
+// one block per run of cells of a single cell row, which staged nine windows' worth of atoms per
+// center instead of 3.4 and had one lane per center (this kernel in forced builds of films with
+// 0.05 A of noise, us): 8M atoms 1303 against 1413, 1M 168 against 201, 216k 47 against 65, with
+// the paper's form 402 against 623, its outer lists 1407 against 4165, the 10k-atom film of the
+// paper's protocol 55 against 185, a 2k-atom bulk 18 against 34.  Held to 6 wavefronts per SIMD (three blocks per compute unit): at 5
 // two blocks fit and the 8M film takes 1.55 ms, at 7 or 8 the registers spill (1.46).
 
 // Image shift (FP64) along an axis of an unwrapped cell coordinate u of a grid of g cells.
@@ -1388,7 +1392,7 @@ __global__ __launch_bounds__(BLOCK) void k_xlist(Consts K, BuildArgs A) {
 // bounds the refill is the gather of one position per source entry: the paper's form has about
 // 940 outer entries an atom and 260 middle ones.  On the 216k-atom film the refill from the outer
 // list took 787 us a step, from the middle one 222 (4 lanes an atom 231, 16 262), and the middle
-// list itself takes 940.
+// list itself takes 960, its check 180 a call.
 constexpr int INNER_G = 8;
 constexpr int MID_G = 16;
 
