@@ -92,8 +92,8 @@ struct md_system {
   int tile_grid = 2048;
   int cus = 256;
   int list_parts = 0;    // blocks per work item of the list build that md_params.list_tgt asks for (0: none)
-  int list_grid = 0;     // blocks of the list build that MD_LIST_PERSISTENT in the environment at
-                         // creation asks for (0: list_blocks decides; results do not depend on it)
+  bool list_stride = false;   // MD_LIST_PERSISTENT=1 in the environment at creation: an eighth of the
+                              // list build's blocks, each striding over several shares (tests)
   int static_dev = -1;   // device whose static scratch is the workspace (md_workspace_bind_static)
 };
 
@@ -253,12 +253,12 @@ int list_parts(const md_system* s) {
 // The bricks expected are those of the boxes given, which may be higher than the atoms reach (an
 // indenter above a film), and then cut into larger bricks than the build finds; so no fewer blocks
 // than one per 300 atoms either (items have 300 to 500): 308 blocks for the 330 items of a
-// 101k-atom film made the last ones wait for a second round, 108 us a forced build against 97.
+// 101k-atom film made the last ones wait for a second round, 108 us a forced build against 91.
 constexpr int LIST_WAVES = 16;
 int list_blocks(const md_system* s) {
-  if (s->list_grid > 0) return s->list_grid;
   const int64_t items = std::min<int64_t>(std::max<int64_t>(s->best + s->best / 4, s->ntot / 300) + 8, s->ntot);
-  return (int)std::min<int64_t>(items * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
+  const int64_t blocks = std::min<int64_t>(items * list_parts(s), (int64_t)s->cus * 3 * LIST_WAVES);
+  return (int)(s->list_stride ? (blocks + 7) / 8 : blocks);
 }
 
 // Grid of the kernels that walk the near-indenter atoms (one wavefront per atom, grid-stride).
@@ -609,7 +609,7 @@ MD_API int md_system_create(const md_replica_desc* reps, int32_t nrep, const md_
     const char* fe = std::getenv("MD_FUSE_ENERGY");
     s->fuse_energy = !(fe && std::atoi(fe) == 0);
     const char* lp = std::getenv("MD_LIST_PERSISTENT");
-    s->list_grid = lp ? std::min(std::max(std::atoi(lp), 0), 1 << 20) : 0;
+    s->list_stride = lp && std::atoi(lp) != 0;
   }
   s->L = make_layout(*s);
   *out = s;
